@@ -5,10 +5,10 @@
 //   d  = M2 relu(M1 h')   (or M h')
 //
 // Patches are the rows of tall-skinny products.  A workgroup takes 64 patch
-// rows; each of its four wave64s owns 16 of them and runs the whole chain on
-// 16 x 16 MFMA tiles with FP32 accumulation:
+// rows (128 in the wide kernel); its waves own hidden tiles of 16 units and run
+// the whole chain on 16 x 16 MFMA tiles with FP32 accumulation:
 //   phase 1: [x | h] against the stacked gate weights [W_g | U_g] (U_h part 0),
-//   gates in registers, r*h to LDS (rows private to the wave),
+//   gates in registers, r*h to LDS,
 //   phase 2: (r*h) against U_h, then the update of h (FP32 state),
 //   MLP: h' -> LDS -> M1 -> relu -> LDS -> M2 -> per-patch output.
 // Operands are FP32 (v_mfma_f32_16x16x4_f32) or BF16 with round-to-nearest-
@@ -91,203 +91,263 @@ template <> struct Op<1> {
 };
 
 
-// One 64-patch tile.  Wave w takes row tiles 2 (w & 1) and 2 (w & 1) + 1 and
-// half of the hidden (and MLP output) tiles, w >> 1, so that every weight
-// fragment it reads feeds two row tiles and the workgroup reads each weight
-// fragment twice.  HMC is the MLP hidden width rounded up to 64, 128 or 256
-// (0 without the hidden layer): it sizes the LDS.
-template <int PREC, int H, int HMC>
-__device__ __forceinline__ void net_tile(const FlowArgs &f, int blk, NetArgs net)
+// Streamed kernel: FP32 operands, and the BF16 shapes that the persistent
+// kernels below do not cover (H = 32, 96; the paper's network; the reset after
+// U_h; an MLP width other than 0 or H).
+//
+// A workgroup takes 64 patches.  Wave w owns hidden tile w % HT for RT of the
+// four row tiles, so the workgroup reads each weight fragment once from L2 (twice
+// at H = 32) and every fragment feeds RT row tiles.  The operand rows
+// [x | h | 0] lie in LDS at a pitch of an odd number of 16-byte pieces (the 16
+// rows of a fragment read fall in distinct banks); once the gate products are
+// done the same bytes hold r * h, h' and the MLP hidden layer.  Products are
+// formed transposed (weights x activations^T), so that lane (li, lq) holds patch
+// row 16 rt + li and the four units ucol = 16 ht + 4 lq .. + 3: the state is read once,
+// in that layout (the operand and the update share it), and state, r * h, h' and
+// outputs move as vectors.  The gate fragments of the next AHEAD k-chunks are
+// requested before a chunk's products.  The k-chunks that hold the state alone
+// skip the candidate gate, whose weights there are zero (164 of 180 products of a
+// row tile and hidden tile at K = 2, H = Hm = 64).
+// FP32 is bound by the matrix cores: 656 products of 32 cycles per 16 patches at
+// that shape, 140 us for 1024 x 256 patches at 2.4 GHz (164 us at the 134 TFLOP/s
+// that a register-only loop of this instruction reaches); 286 -> 204 us against
+// wave pairs that read every weight fragment twice and the rows from global
+// memory inside the k-loop.  Eight waves of two row tiles measured slower (232 us).
+struct StreamRows {
+    int lda, bytes;   // row pitch in elements, and LDS bytes of the tile
+};
+template <int PREC, int H>
+__host__ __device__ inline StreamRows stream_rows(int kc1, int Hm)
+{
+    typedef Op<PREC> O;
+    constexpr int V = 16 / (int)sizeof(typename O::T);
+    StreamRows r;
+    const int w = kc1 * O::KC;
+    r.lda = (w / V) % 2 ? w : w + V;
+    const int ldh = H + V, ldm = Hm > 0 ? Hm + V : 0;
+    const int tail = ldh + (ldh > ldm ? ldh : ldm);      // h', then r * h and the MLP hidden layer
+    r.bytes = kNetRows * (r.lda > tail ? r.lda : tail) * (int)sizeof(typename O::T);
+    return r;
+}
+
+// Waves of a workgroup: one per hidden tile, at least four; at H = 96 two per
+// hidden tile (six waves would load the four SIMDs unevenly: 300 x 200 patches,
+// K = 2, FP32 step 159.8 -> 140.1 us), and registers for two workgroups per CU.
+template <int H> constexpr int stream_waves() { return H == 96 ? 12 : (H / 16 < 4 ? 4 : H / 16); }
+template <int H> constexpr int stream_simd_waves() { return H == 96 ? 6 : 2; }
+
+template <int PREC, int H>
+__device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const NetArgs &net, unsigned char *lds)
 {
     typedef Op<PREC> O;
     typedef typename O::T T;
     typedef typename O::Frag Frag;
-    constexpr int KC = O::KC, KQ = O::KQ;
-    constexpr int HT = H / 16, HW = HT / 2;    // hidden-unit tiles, per wave
-    static_assert(HT % 2 == 0, "hidden tiles split over two wave pairs");
-    constexpr int PAD = 16 / sizeof(T);        // 16-byte row padding
-    constexpr int LDH = H + PAD;
-    constexpr int LDM = HMC + PAD;
-
-    // r*h (phase 2 operand) and the MLP hidden layer share one buffer: the
-    // former is dead once phase 2 is done.  Rows are the tile's 64 patches.
-    constexpr int LDB = LDH > LDM ? LDH : LDM;
-    __shared__ __align__(16) T sBuf[kNetRows * LDB];
-    __shared__ __align__(16) T sHp[kNetRows * LDH];
-    T *sR = sBuf, *sAm = sBuf;
+    constexpr int KC = O::KC, KQ = O::KQ, HC = H / KC, V = 16 / (int)sizeof(T);
+    constexpr int HT = H / 16, NW = stream_waves<H>(), NT = 64 * NW, RT = 4 * HT / NW;
+    constexpr int AHEAD = PREC == 0 ? 1 : 2;     // k-chunks requested ahead: a chunk's products take 4 times as long in FP32
+    constexpr int LDH = H + V;
+    typedef T T4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(1))) float gfloat;
+    typedef __attribute__((address_space(1))) f4 gf4;
+    typedef float v2 __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(1))) v2 gv2;
 
     const int P = f.nx * f.ny;
     const int nin = net.nin, nout = net.nout, Hm = net.Hm, kc1 = net.kc1;
     const bool reset_after = net.reset_after != 0;
-    // (tile_thread(): in the batched tile loop the index math is redone per
-    // tile instead of hoisted out of the loop and held in registers)
+    const int lda = stream_rows<PREC, H>(kc1, Hm).lda, ldm = Hm + V;
     const int tid = tile_thread();
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int li = lane & 15, lq = lane >> 4;
-    const int rg = wave & 1, hg = wave >> 1;
-    // the flow's buffers through global address-space pointers: global, not
-    // flat, memory instructions where the pointers come from the batch table
-    typedef __attribute__((address_space(1))) float gfloat;
-    const gptr<T> Xg = (gptr<T>)f.X;
-    gfloat *const hG = (gfloat *)f.h;
-    gfloat *const dG = (gfloat *)f.dpatch;
-    const int r0 = 32 * rg;                         // first tile-local row of this wave
-    const int rbase = blk * kNetRows + r0;          // first patch row of this wave
+    const int ht = wave % HT, rt0 = RT * (wave / HT);
+    const int ucol = 16 * ht + 4 * lq;
+    const int row0 = blk * kNetRows, nrows = min(kNetRows, P - row0);
 
-    const Frag *B1 = reinterpret_cast<const Frag *>(net.B1);
-    const Frag *B2 = reinterpret_cast<const Frag *>(net.B2);
-    const Frag *B3 = reinterpret_cast<const Frag *>(net.B3);
-    const Frag *B4 = reinterpret_cast<const Frag *>(net.B4);
+    T *const sA = reinterpret_cast<T *>(lds);          // [x | h | 0]
+    T *const sHp = sA, *const sR = sA + kNetRows * LDH, *const sAm = sR;
+    const gptr<Frag> B1 = pinned<Frag>(net.B1);
+    const gptr<Frag> B2 = pinned<Frag>(net.B2);
+    const gptr<Frag> B3 = pinned<Frag>(net.B3);
+    const gptr<Frag> B4 = pinned<Frag>(net.B4);
+    gfloat *const hG = (gfloat *)(f.h + (size_t)row0 * H);
+    gfloat *const dG = (gfloat *)(f.dpatch + (size_t)row0 * nout);
 
-    // ---- phase 1: [x | h] x [W_g | U_g]^T for g = z, r, h
-    f4 az[HW][2], ar[HW][2], ah[HW][2];
+    // ---- the tile's rows to LDS.  x: consecutive 16-byte pieces of memory
+    //      (unconditional loads: those past the mesh's last row read its
+    //      last piece, and such rows' results are never stored); h: in the
+    //      lanes' own layout.
+    {
+        typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(1))) const u4 gu4;
+        gu4 *const X = (gu4 *)(reinterpret_cast<const T *>(f.X) + (size_t)row0 * nin);
+        const unsigned pr = (unsigned)nin / V, np = kNetRows * pr, in = (unsigned)nrows * pr;   // pieces per row, per tile, inside
+        const unsigned inv = ((1u << 24) + pr - 1) / pr;      // c / pr = c inv >> 24 (c < 64 pr, pr < 128: exact)
+        constexpr int U = PREC == 0 ? 7 : 4;
+        for (unsigned c0 = tid; c0 < np; c0 += U * NT) {
+            u4 x[U];
 #pragma unroll
-    for (int t = 0; t < HW; ++t)
+            for (int u = 0; u < U; ++u) x[u] = X[min(c0 + u * NT, in - 1)];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) az[t][q] = ar[t][q] = ah[t][q] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int kc = 0; kc < kc1; ++kc) {
-        const int k0 = kc * KC + lq * KQ;
-        Frag a[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int arow = rbase + 16 * q + li;      // row this lane supplies operand values for
-            if (arow < P && k0 < nin) a[q] = O::load_x(Xg, (size_t)arow * nin + k0);
-            else if (arow < P && k0 < nin + H) a[q] = O::load_f32((gptr<float>)(hG + (size_t)arow * H + (k0 - nin)));
-            else {
-#pragma unroll
-                for (int e = 0; e < KQ; ++e) a[q][e] = O::cvt(0.f);
-            }
-        }
-#pragma unroll
-        for (int tw = 0; tw < HW; ++tw) {
-            const int t = hg * HW + tw;
-            const Frag wz = B1[((0 * HT + t) * kc1 + kc) * 64 + lane];
-            const Frag wr = B1[((1 * HT + t) * kc1 + kc) * 64 + lane];
-            const Frag wh = B1[((2 * HT + t) * kc1 + kc) * 64 + lane];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                az[tw][q] = O::mma(az[tw][q], a[q], wz);
-                ar[tw][q] = O::mma(ar[tw][q], a[q], wr);
-                ah[tw][q] = O::mma(ah[tw][q], a[q], wh);
+            for (int u = 0; u < U; ++u) {
+                const unsigned c = c0 + u * NT, r = c * inv >> 24;
+                if (c < np) *reinterpret_cast<u4 *>(&sA[r * lda + V * (c - r * pr)]) = x[u];
             }
         }
     }
-
-    // ---- gates; r*h to LDS.  Lane holds rows 16 q + 4 lq + e (of the
-    //      wave's 32), column 16 t + li.
-    float hold[HW][2][4];
+    f4 hold[RT];
 #pragma unroll
-    for (int tw = 0; tw < HW; ++tw)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int lr = r0 + 16 * q + 4 * lq + e, row = blk * kNetRows + lr, k = 16 * (hg * HW + tw) + li;
-                const float h0 = row < P ? hG[(size_t)row * H + k] : 0.f;
-                hold[tw][q][e] = h0;
-                // (BF16 weights come pre-multiplied for 2^x, see sigmoid_l2)
-                az[tw][q][e] = PREC == 1 ? sigmoid_l2(az[tw][q][e]) : sigmoid(az[tw][q][e]);
-                const float r = PREC == 1 ? sigmoid_l2(ar[tw][q][e]) : sigmoid(ar[tw][q][e]);
-                // reset after U_h: phase 2 takes h itself, r stays for the candidate
-                ar[tw][q][e] = r;
-                sR[lr * LDH + k] = O::cvt(reset_after ? h0 : r * h0);
-            }
-    __syncthreads();
-
-    // ---- phase 2: (r*h) x U_h^T (or h x U_h^T, then times r); update h
-    f4 au[HW][2];
-#pragma unroll
-    for (int tw = 0; tw < HW; ++tw)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) au[tw][q] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kc = 0; kc < H / KC; ++kc) {
-        Frag a[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) a[q] = *reinterpret_cast<const Frag *>(&sR[(r0 + 16 * q + li) * LDH + kc * KC + lq * KQ]);
-#pragma unroll
-        for (int tw = 0; tw < HW; ++tw) {
-            const Frag w = B2[((hg * HW + tw) * (H / KC) + kc) * 64 + lane];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) au[tw][q] = O::mma(au[tw][q], a[q], w);
-        }
+    for (int q = 0; q < RT; ++q) {
+        const int r = 16 * (rt0 + q) + li;
+        hold[q] = *(gf4 *)(hG + min(r, nrows - 1) * H + ucol);
     }
-#pragma unroll
-    for (int tw = 0; tw < HW; ++tw)
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int lr = r0 + 16 * q + 4 * lq + e, row = blk * kNetRows + lr, k = 16 * (hg * HW + tw) + li;
-                const float z = az[tw][q][e];
-                const float u = reset_after ? ar[tw][q][e] * au[tw][q][e] : au[tw][q][e];
-                const float hh = PREC == 1 ? tanh_l2(ah[tw][q][e] + u) : fast_tanh(ah[tw][q][e] + u);
-                const float hn = hh + z * (hold[tw][q][e] - hh);   // z h + (1 - z) hh
-                if (row < P) hG[(size_t)row * H + k] = hn;
-                sHp[lr * LDH + k] = O::cvt(hn);
-            }
-    __syncthreads();
-
-    // ---- MLP head; the wave pair hg takes every other output tile
-    const int ot_n = (nout + 15) / 16;
-    auto out_tile = [&](int ot, const T *src, int ld, int kcn, const Frag *Bw) {
-        f4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        for (int kc = 0; kc < kcn; ++kc) {
-            const Frag w = Bw[(ot * kcn + kc) * 64 + lane];
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-                acc[q] = O::mma(acc[q], *reinterpret_cast<const Frag *>(&src[(r0 + 16 * q + li) * ld + kc * KC + lq * KQ]), w);
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = rbase + 16 * q + 4 * lq + e, o = 16 * ot + li;
-                if (row < P && o < nout) dG[(size_t)row * nout + o] = acc[q][e];
-            }
+    Frag w[AHEAD][3];
+    const int kcx = (nin + KC - 1) / KC;            // chunks with input columns
+    auto fetch = [&](int kc, Frag (&d)[3]) {
+        const int k = min(kc, kc1 - 1);
+        d[0] = B1[((0 * HT + ht) * kc1 + k) * 64 + lane];
+        d[1] = B1[((1 * HT + ht) * kc1 + k) * 64 + lane];
+        d[2] = B1[((2 * HT + ht) * kc1 + min(k, kcx - 1)) * 64 + lane];
     };
-    if constexpr (HMC > 0) {
-        for (int mt = hg; mt < Hm / 16; mt += 2) {
-            f4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-            for (int kc = 0; kc < H / KC; ++kc) {
-                const Frag w = B3[(mt * (H / KC) + kc) * 64 + lane];
+    for (int i = 0; i < AHEAD; ++i) fetch(i, w[i]);
 #pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    acc[q] = O::mma(acc[q], *reinterpret_cast<const Frag *>(&sHp[(r0 + 16 * q + li) * LDH + kc * KC + lq * KQ]), w);
+    for (int q = 0; q < RT; ++q) {
+        const int r = 16 * (rt0 + q) + li;
+        T4 hb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) hb[e] = O::cvt(hold[q][e]);
+        *reinterpret_cast<T4 *>(&sA[r * lda + nin + ucol]) = hb;
+    }
+    for (int z = nin + H + 4 * (tid & 3); z < kc1 * KC; z += 16)       // the k-padding
+        for (int r = tid >> 2; r < kNetRows; r += NT / 4) *reinterpret_cast<T4 *>(&sA[r * lda + z]) = T4{};
+    __syncthreads();
+
+    // ---- phase 1: [x | h] against [W_g | U_g], g = z, r, h (U_h comes in phase 2)
+    f4 az[RT], ar[RT], ah[RT];
+#pragma unroll
+    for (int q = 0; q < RT; ++q) az[q] = ar[q] = ah[q] = f4{0.f, 0.f, 0.f, 0.f};
+    const T *const arow = sA + (16 * rt0 + li) * lda + lq * KQ;
+    auto chunk = [&](int kc, bool cand) {
+        Frag nw[3];
+        fetch(kc + AHEAD, nw);
+        __builtin_amdgcn_sched_barrier(0);   // (the loads stay ahead of the products)
+#pragma unroll
+        for (int q = 0; q < RT; ++q) {
+            const Frag a = *reinterpret_cast<const Frag *>(&arow[16 * q * lda + kc * KC]);
+            az[q] = O::mma(az[q], w[0][0], a);
+            ar[q] = O::mma(ar[q], w[0][1], a);
+            if (cand) ah[q] = O::mma(ah[q], w[0][2], a);
+        }
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+            for (int g = 0; g < 3; ++g) w[i][g] = i + 1 < AHEAD ? w[i + 1][g] : nw[g];
+    };
+#pragma unroll 1
+    for (int kc = 0; kc < kcx; ++kc) chunk(kc, true);
+#pragma unroll 1
+    for (int kc = kcx; kc < kc1; ++kc) chunk(kc, false);
+    Frag w2[HC];
+#pragma unroll
+    for (int kc = 0; kc < HC; ++kc) w2[kc] = B2[(ht * HC + kc) * 64 + lane];
+    __syncthreads();   // every wave is done with the operand rows
+
+    // ---- gates; r*h to LDS (reset after U_h: h itself, r kept for the candidate)
+#pragma unroll
+    for (int q = 0; q < RT; ++q) {
+        const int r = 16 * (rt0 + q) + li;
+        T4 rh;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // (BF16 weights come pre-multiplied for 2^x, see sigmoid_l2)
+            az[q][e] = PREC == 1 ? sigmoid_l2(az[q][e]) : sigmoid(az[q][e]);
+            ar[q][e] = PREC == 1 ? sigmoid_l2(ar[q][e]) : sigmoid(ar[q][e]);
+            rh[e] = O::cvt(reset_after ? hold[q][e] : ar[q][e] * hold[q][e]);
+        }
+        *reinterpret_cast<T4 *>(&sR[r * LDH + ucol]) = rh;
+    }
+    __syncthreads();
+
+    // ---- phase 2: U_h (r*h) (or U_h h, then times r); new state
+    f4 au[RT];
+#pragma unroll
+    for (int q = 0; q < RT; ++q) au[q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < HC; ++kc)
+#pragma unroll
+        for (int q = 0; q < RT; ++q)
+            au[q] = O::mma(au[q], w2[kc], *reinterpret_cast<const Frag *>(&sR[(16 * (rt0 + q) + li) * LDH + kc * KC + lq * KQ]));
+#pragma unroll
+    for (int q = 0; q < RT; ++q) {
+        const int r = 16 * (rt0 + q) + li;
+        f4 hn;
+        T4 hb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float z = az[q][e];
+            const float u = reset_after ? ar[q][e] * au[q][e] : au[q][e];
+            const float hh = PREC == 1 ? tanh_l2(ah[q][e] + u) : fast_tanh(ah[q][e] + u);
+            hn[e] = hh + z * (hold[q][e] - hh);   // z h + (1 - z) hh
+            hb[e] = O::cvt(hn[e]);
+        }
+        if (r < nrows) *(gf4 *)(hG + r * H + ucol) = hn;
+        *reinterpret_cast<T4 *>(&sHp[r * LDH + ucol]) = hb;
+    }
+    __syncthreads();
+
+    // ---- MLP head; the wave takes hidden and output tiles ht, ht + HT, ...
+    auto product = [&](f4 (&acc)[RT], const T *src, int ld, int kcn, gptr<Frag> Bw, int tile) {
+#pragma unroll
+        for (int q = 0; q < RT; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+        Frag wk = Bw[(tile * kcn) * 64 + lane];
+        for (int kc = 0; kc < kcn; ++kc) {
+            const Frag wn = Bw[(tile * kcn + min(kc + 1, kcn - 1)) * 64 + lane];
+#pragma unroll
+            for (int q = 0; q < RT; ++q)
+                acc[q] = O::mma(acc[q], wk, *reinterpret_cast<const Frag *>(&src[(16 * (rt0 + q) + li) * ld + kc * KC + lq * KQ]));
+            wk = wn;
+        }
+    };
+    const int ot_n = (nout + 15) / 16;
+    f4 acc[RT];
+    if (Hm > 0) {
+        for (int mt = ht; mt < Hm / 16; mt += HT) {
+            product(acc, sHp, LDH, HC, B3, mt);
+#pragma unroll
+            for (int q = 0; q < RT; ++q) {
+                T4 m;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m[e] = O::cvt(fmaxf(acc[q][e], 0.f));
+                *reinterpret_cast<T4 *>(&sAm[(16 * (rt0 + q) + li) * ldm + 16 * mt + 4 * lq]) = m;
             }
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    sAm[(r0 + 16 * q + 4 * lq + e) * LDM + 16 * mt + li] = O::cvt(fmaxf(acc[q][e], 0.f));
         }
         __syncthreads();
-        for (int ot = hg; ot < ot_n; ot += 2) out_tile(ot, sAm, LDM, Hm / KC, B4);
-    } else {
-        for (int ot = hg; ot < ot_n; ot += 2) out_tile(ot, sHp, LDH, H / KC, B3);
     }
-}
-
-// MLP hidden width class of the generic kernel (LDS sizing).
-static constexpr int hm_class(int Hm) { return Hm == 0 ? 0 : (Hm <= 64 ? 64 : (Hm <= 128 ? 128 : 256)); }
-
-// Waves per SIMD of the generic kernel: two workgroups per CU where the LDS
-// allows it.
-template <int PREC, int H, int HMC>
-constexpr int net_waves()
-{
-    constexpr int sz = PREC == 0 ? 4 : 2, pad = 16 / sz, ldh = H + pad, ldm = HMC + pad;
-    return kNetRows * ((ldh > ldm ? ldh : ldm) + ldh) * sz <= 80 * 1024 ? 2 : 1;
+    for (int ot = ht; ot < ot_n; ot += HT) {
+        if (Hm > 0) product(acc, sAm, ldm, Hm / KC, B4, ot);
+        else product(acc, sHp, LDH, HC, B3, ot);
+        const int oc = 16 * ot + 4 * lq;
+#pragma unroll
+        for (int q = 0; q < RT; ++q) {
+            const int r = 16 * (rt0 + q) + li;
+            // nout is even: the pairs (oc, oc+1), (oc+2, oc+3) are inside or outside together
+            if (r < nrows) {
+                gfloat *o = dG + r * nout + oc;
+                if (oc < nout) *(gv2 *)o = v2{acc[q][0], acc[q][1]};
+                if (oc + 2 < nout) *(gv2 *)(o + 2) = v2{acc[q][2], acc[q][3]};
+            }
+        }
+    }
 }
 
 // Single flow: one tile per block.  Batched: the blocks stride over the
 // table's tiles of all flows, so the grid need not match the batch.
-template <int PREC, int H, int HMC, bool BATCHED>
-__global__ __launch_bounds__(kThreads, (net_waves<PREC, H, HMC>())) void k_net(FlowArgs single, const BatchTable *__restrict__ bt, NetArgs net)
+template <int PREC, int H, bool BATCHED>
+__global__ __launch_bounds__(64 * stream_waves<H>(), stream_simd_waves<H>()) void k_net(FlowArgs single, const BatchTable *__restrict__ bt, NetArgs net)
 {
+    extern __shared__ __align__(16) unsigned char s_rows[];
     if (!BATCHED) {
-        net_tile<PREC, H, HMC>(single, blockIdx.x, net);
+        stream_tile<PREC, H>(single, blockIdx.x, net, s_rows);
         return;
     }
     const int total = bt->prefix[kKindNet][bt->nflows];
@@ -295,7 +355,7 @@ __global__ __launch_bounds__(kThreads, (net_waves<PREC, H, HMC>())) void k_net(F
     for (int g = blockIdx.x; g < total; g += gridDim.x) {
         int blk = g;
         const FlowArgs &f = *batch_flow(bt, kKindNet, blk);
-        net_tile<PREC, H, HMC>(f, blk, net);
+        stream_tile<PREC, H>(f, blk, net, s_rows);
         __syncthreads();   // LDS is reused by the next tile
     }
 }
@@ -1512,23 +1572,14 @@ int net_blocks(const NetArgs &net, int row_tiles)
     return row_tiles;
 }
 
-template <int PREC, int H, int HMC>
-static void launch_net_m(const FlowArgs &f, const BatchTable *bt, int nblocks, const NetArgs &net, hipStream_t s)
-{
-    if (bt) hipLaunchKernelGGL((k_net<PREC, H, HMC, true>), dim3(nblocks), dim3(kThreads), 0, s, f, bt, net);
-    else hipLaunchKernelGGL((k_net<PREC, H, HMC, false>), dim3(nblocks), dim3(kThreads), 0, s, f, bt, net);
-}
-
 template <int PREC, int H>
 static hipError_t launch_net_t(const FlowArgs &f, const BatchTable *bt, int nblocks, const NetArgs &net,
                                hipStream_t s)
 {
-    switch (hm_class(net.Hm)) {
-    case 0: launch_net_m<PREC, H, 0>(f, bt, nblocks, net, s); break;
-    case 64: launch_net_m<PREC, H, 64>(f, bt, nblocks, net, s); break;
-    case 128: launch_net_m<PREC, H, 128>(f, bt, nblocks, net, s); break;
-    default: launch_net_m<PREC, H, 256>(f, bt, nblocks, net, s);
-    }
+    const int lds = stream_rows<PREC, H>(net.kc1, net.Hm).bytes;
+    const dim3 g(nblocks), b(64 * stream_waves<H>());
+    if (bt) hipLaunchKernelGGL((k_net<PREC, H, true>), g, b, lds, s, f, bt, net);
+    else hipLaunchKernelGGL((k_net<PREC, H, false>), g, b, lds, s, f, bt, net);
     return hipGetLastError();
 }
 
