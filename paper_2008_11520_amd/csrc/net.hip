@@ -631,28 +631,38 @@ __global__ __launch_bounds__(kThreads) void k_net_fp8(FlowArgs single, const Bat
     }
 }
 
-// Persistent BF16 kernel for H = 64 (and Hm 0 or 64).  Eight waves: wave w
-// owns hidden tile w % 4 for row tiles 2 (w / 4) and 2 (w / 4) + 1 of each
-// 64-patch tile, and keeps that hidden tile's weight fragments (three gates,
-// U_h, M1 and M2 / M) in registers for the whole launch.  The workgroup loops
-// over 64-patch row tiles staged through LDS, so each weight fragment is read
-// from memory once per workgroup.
-constexpr int kNetH64Threads = 512;
+// Persistent BF16 kernel for K <= 2 and H <= 96 (Hm 0 or H), NIN input columns.
+// Two waves per hidden tile: wave w owns hidden tile w % HT for row tiles
+// 2 (w / HT) and 2 (w / HT) + 1 of each 64-patch tile, and keeps that hidden
+// tile's weight fragments (three gates, U_h) in registers for the whole launch;
+// the MLP and output fragments lie in LDS.  The workgroup loops over 64-patch
+// row tiles staged through LDS, so each weight fragment is read from memory
+// once per workgroup and the loads in flight are the next tiles' rows alone.
+// Bound by HBM and the five barriers of a tile: at 1024 x 256 patches and K = 2
+// H = 64 takes 56.5 us (241 MB), H = 96 with the paper's input 70 us (308 MB; the
+// streamed kernel, which holds two workgroups of six waves per CU and waits for
+// its rows at each tile's start, 126 us).  Any spill inside the loop waits for
+// the rows in flight (100 us with a second prefetch buffer at H = 96).
+constexpr int kNetH64Threads = 512;   // the persistent wide and FP8 kernels
+template <int H> constexpr int net_reg_threads() { return 8 * H; }
 
-template <int K>
-__global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, const BatchTable *__restrict__ bt, NetArgs net,
-                                                               int ntiles)
+template <int NIN, int H>
+__global__ __launch_bounds__(net_reg_threads<H>(), (H == 96 ? 3 : 2)) void k_net_reg(FlowArgs single, const BatchTable *__restrict__ bt,
+                                                                                     NetArgs net, int ntiles)
 {
     typedef Op<1> O;
-    constexpr int H = 64, KC = 32, KQ = 8, HT = 4, RTW = 2;
-    constexpr int n = 1 << K, nf = (n + 1) * (n + 1), nin = 4 * nf + 4, nout = 2 * nf;
+    constexpr int NT = net_reg_threads<H>();
+    constexpr int KC = 32, KQ = 8, HT = H / 16, HC = H / KC, RTW = 2;
+    constexpr int K = NIN == 104 ? 2 : 1, n = 1 << K, nf = (n + 1) * (n + 1), nin = NIN, nout = 2 * nf;
     if (bt) ntiles = bt->prefix[kKindNet][bt->nflows];   // batched: the table's row tiles
-    constexpr int KC1 = (nin + H + KC - 1) / KC;
-    constexpr int LDA = KC1 * KC + 8;          // +16 bytes per row
+    constexpr int KC1 = (nin + H + KC - 1) / KC, KCX = (nin + KC - 1) / KC;   // k-chunks; those with input columns
+    // row pitch: an odd number of 16-byte pieces
+    constexpr int LDA = (KC1 * KC / 8) % 2 ? KC1 * KC : KC1 * KC + 8;
     constexpr int LDH = H + 8;
-    constexpr int OT = (nout + 15) / 16;       // output tiles (<= 4 here)
+    constexpr int OT = (nout + 15) / 16;       // output tiles
+    constexpr int WT = HT > OT ? HT : OT;
     constexpr int PADK = KC1 * KC - nin - H;
-    static_assert(OT <= 4, "one output tile per hidden-tile slot");
+    static_assert((H == 32 || H == 64 || H == 96) && nin % 8 == 0, "two waves per hidden tile, rows in 16-byte pieces");
 
     __shared__ __align__(16) __bf16 sA[64 * LDA];
     constexpr int LDS32 = H + 4;              // FP32 state rows, padded against bank conflicts
@@ -663,36 +673,46 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int li = lane & 15, lq = lane >> 4;
-    const int ht = wave & 3, rt0 = RTW * (wave >> 2);
+    const int ht = wave % HT, rt0 = RTW * (wave / HT);
     const int Hm = net.Hm;
+    const bool reset_after = net.reset_after != 0;
     const bf8 *B1 = reinterpret_cast<const bf8 *>(net.B1);
     const bf8 *B2 = reinterpret_cast<const bf8 *>(net.B2);
     const bf8 *B3 = reinterpret_cast<const bf8 *>(net.B3);
     const bf8 *B4 = reinterpret_cast<const bf8 *>(net.B4);
 
-    // gate and U_h fragments in registers; the MLP fragments in LDS
-    __shared__ __align__(16) bf8 sW3[4 * (H / KC) * 64];
-    __shared__ __align__(16) bf8 sW4[4 * (H / KC) * 64];
-    bf8 w1[3][KC1], w2[H / KC];
+    // gate and U_h fragments in registers (the candidate's weights are zero in
+    // the chunks of state alone); the MLP fragments in LDS
+    __shared__ __align__(16) bf8 sW3[WT * HC * 64];
+    __shared__ __align__(16) bf8 sW4[OT * HC * 64];
+    constexpr bool W2R = H < 96;               // (at H = 96 U_h lies in LDS too: 12 waves leave 168 registers each)
+    __shared__ __align__(16) bf8 sW2[W2R ? 1 : HT * HC * 64];
+    bf8 wz[KC1], wr[KC1], wh[KCX], w2[W2R ? HC : 1];
 #pragma unroll
-    for (int g = 0; g < 3; ++g)
-#pragma unroll
-        for (int kc = 0; kc < KC1; ++kc) w1[g][kc] = B1[((g * HT + ht) * KC1 + kc) * 64 + lane];
-#pragma unroll
-    for (int kc = 0; kc < H / KC; ++kc) w2[kc] = B2[(ht * (H / KC) + kc) * 64 + lane];
-    for (int t = tid; t < 4 * (H / KC) * 64; t += kNetH64Threads) {
-        const int tile_m = t / ((H / KC) * 64);
-        sW3[t] = (Hm > 0 || tile_m < OT) ? B3[t] : bf8{};
-        sW4[t] = (Hm > 0 && tile_m < OT) ? B4[t] : bf8{};
+    for (int kc = 0; kc < KC1; ++kc) {
+        wz[kc] = B1[((0 * HT + ht) * KC1 + kc) * 64 + lane];
+        wr[kc] = B1[((1 * HT + ht) * KC1 + kc) * 64 + lane];
     }
+#pragma unroll
+    for (int kc = 0; kc < KCX; ++kc) wh[kc] = B1[((2 * HT + ht) * KC1 + kc) * 64 + lane];
+    if constexpr (W2R) {
+#pragma unroll
+        for (int kc = 0; kc < HC; ++kc) w2[kc] = B2[(ht * HC + kc) * 64 + lane];
+    } else {
+        for (int t = tid; t < HT * HC * 64; t += NT) sW2[t] = B2[t];
+    }
+    const int n3 = (Hm > 0 ? HT : OT) * HC * 64;      // fragments of M1, or of M
+    for (int t = tid; t < n3; t += NT) sW3[t] = B3[t];
+    if (Hm > 0)
+        for (int t = tid; t < OT * HC * 64; t += NT) sW4[t] = B4[t];
 
     // Tiles are contiguous in memory: the network input (BF16, 64 x nin) and
     // the state (FP32, 64 x H).  Each thread prefetches its 16-byte pieces of
     // the next two tiles into two register buffers while the current one is
     // computed, so two tiles' loads are in flight per workgroup.
     constexpr int XCH = 64 * nin / 8, HCH = 64 * H / 4;            // 16-byte pieces per tile
-    constexpr int XPT = (XCH + kNetH64Threads - 1) / kNetH64Threads;
-    constexpr int HPT = (HCH + kNetH64Threads - 1) / kNetH64Threads;
+    constexpr int XPT = (XCH + NT - 1) / NT;
+    constexpr int HPT = (HCH + NT - 1) / NT;
     bf8 xrA[XPT], xrB[XPT];
     f4 hrA[HPT], hrB[HPT];
     // A row tile's buffers.  The fields are read in two branches: a pointer
@@ -735,21 +755,23 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
         const int t0 = tile_thread();
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
-            const int c = t0 + i * kNetH64Threads;
+            const int c = t0 + i * NT;
             xr[i] = tile_piece_in(c, nin / 8, rw.nrows) ? rw.X[c] : bf8{};
         }
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
-            const int c = t0 + i * kNetH64Threads;
+            const int c = t0 + i * NT;
             hr[i] = tile_piece_in(c, H / 4, rw.nrows) ? ((gf4 *)rw.h)[c] : f4{0.f, 0.f, 0.f, 0.f};
         }
     };
     // the k-padding columns of [x | h] stay zero for the whole launch
     if (PADK > 0)
-        for (int t = tid; t < 64 * PADK; t += kNetH64Threads) sA[(t / PADK) * LDA + nin + H + t % PADK] = (__bf16)0.f;
+        for (int t = tid; t < 64 * PADK; t += NT) sA[(t / PADK) * LDA + nin + H + t % PADK] = (__bf16)0.f;
     const int G = gridDim.x;
+    // (two tiles in flight; one at H = 96, where a second buffer would spill)
+    constexpr bool TWO = H < 96;
     if (blockIdx.x < ntiles) load_tile(blockIdx.x, xrA, hrA);
-    if (blockIdx.x + G < ntiles) load_tile(blockIdx.x + G, xrB, hrB);
+    if (TWO && blockIdx.x + G < ntiles) load_tile(blockIdx.x + G, xrB, hrB);
 
     // one 64-patch tile: stage the prefetched registers, refill them with
     // tile `next`, compute
@@ -763,12 +785,12 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
         const int t1 = tile_thread();
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
-            const int c = t1 + i * kNetH64Threads;
+            const int c = t1 + i * NT;
             if (c < XCH) *reinterpret_cast<bf8 *>(&sA[(c / (nin / 8)) * LDA + 8 * (c % (nin / 8))]) = xr[i];
         }
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
-            const int c = t1 + i * kNetH64Threads;
+            const int c = t1 + i * NT;
             if (c < HCH) {
                 const int r = c / (H / 4), k = 4 * (c % (H / 4));
                 *reinterpret_cast<f4 *>(&sH[r * LDS32 + k]) = hr[i];
@@ -794,9 +816,9 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
                 const bf8 a = *reinterpret_cast<const bf8 *>(&sA[(16 * (rt0 + q) + li) * LDA + kc * KC + lq * KQ]);
-                az[q] = O::mma(az[q], w1[0][kc], a);
-                ar[q] = O::mma(ar[q], w1[1][kc], a);
-                ah[q] = O::mma(ah[q], w1[2][kc], a);
+                az[q] = O::mma(az[q], wz[kc], a);
+                ar[q] = O::mma(ar[q], wr[kc], a);
+                if (kc < KCX) ah[q] = O::mma(ah[q], wh[kc], a);
             }
         f4 hold[RTW];
 #pragma unroll
@@ -807,7 +829,9 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 az[q][e] = sigmoid_l2(az[q][e]);
-                rh[e] = (__bf16)(sigmoid_l2(ar[q][e]) * hold[q][e]);
+                ar[q][e] = sigmoid_l2(ar[q][e]);
+                // (reset after U_h: h itself, r kept for the candidate)
+                rh[e] = (__bf16)(reset_after ? hold[q][e] : ar[q][e] * hold[q][e]);
             }
             *reinterpret_cast<bf4 *>(&sR[r * LDH + ucol]) = rh;
         }
@@ -819,9 +843,9 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
             const int r = 16 * (rt0 + q) + li;
             f4 au = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kc = 0; kc < H / KC; ++kc) {
+            for (int kc = 0; kc < HC; ++kc) {
                 const bf8 a = *reinterpret_cast<const bf8 *>(&sR[r * LDH + kc * KC + lq * KQ]);
-                au = O::mma(au, w2[kc], a);
+                au = O::mma(au, W2R ? w2[W2R ? kc : 0] : sW2[W2R ? 0 : (ht * HC + kc) * 64 + lane], a);
             }
             f4 hn;
             bf4 hb;
@@ -829,7 +853,8 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
             for (int e = 0; e < 4; ++e) {
                 const float z = az[q][e];
                 // h' = z h + (1 - z) c = c + z (h - c), c the candidate state
-                const float c = tanh_l2(ah[q][e] + au[e]);
+                const float u = reset_after ? ar[q][e] * au[e] : au[e];
+                const float c = tanh_l2(ah[q][e] + u);
                 hn[e] = c + z * (hold[q][e] - c);
                 hb[e] = (__bf16)hn[e];
             }
@@ -846,9 +871,9 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
                 const int r = 16 * (rt0 + q) + li;
                 f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kc = 0; kc < H / KC; ++kc) {
+                for (int kc = 0; kc < HC; ++kc) {
                     const bf8 a = *reinterpret_cast<const bf8 *>(&sHp[r * LDH + kc * KC + lq * KQ]);
-                    acc = O::mma(acc, sW3[(ht * (H / KC) + kc) * 64 + lane], a);
+                    acc = O::mma(acc, sW3[(ht * HC + kc) * 64 + lane], a);
                 }
                 bf4 m;
 #pragma unroll
@@ -858,30 +883,35 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
             __syncthreads();
             src = sAm;
         }
-        if (ht < OT) {
+        for (int ot = ht; ot < OT; ot += HT) {
+            const int oc = 16 * ot + 4 * lq;
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
                 const int r = 16 * (rt0 + q) + li;
                 f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kc = 0; kc < H / KC; ++kc) {
+                for (int kc = 0; kc < HC; ++kc) {
                     const bf8 a = *reinterpret_cast<const bf8 *>(&src[r * LDH + kc * KC + lq * KQ]);
-                    acc = O::mma(acc, Hm > 0 ? sW4[(ht * (H / KC) + kc) * 64 + lane] : sW3[(ht * (H / KC) + kc) * 64 + lane], a);
+                    acc = O::mma(acc, Hm > 0 ? sW4[(ot * HC + kc) * 64 + lane] : sW3[(ot * HC + kc) * 64 + lane], a);
                 }
-                // nout is even: the pairs (ucol, ucol+1), (ucol+2, ucol+3) are inside or outside together
+                // nout is even: the pairs (oc, oc+1), (oc+2, oc+3) are inside or outside together
                 if (r < nrows) {
                     typedef float v2 __attribute__((ext_vector_type(2)));
                     typedef __attribute__((address_space(1))) v2 gv2;
-                    gfloat *o = dp + r * nout + ucol;
-                    if (ucol < nout) *(gv2 *)o = v2{acc[0], acc[1]};
-                    if (ucol + 2 < nout) *(gv2 *)(o + 2) = v2{acc[2], acc[3]};
+                    gfloat *o = dp + r * nout + oc;
+                    if (oc < nout) *(gv2 *)o = v2{acc[0], acc[1]};
+                    if (oc + 2 < nout) *(gv2 *)(o + 2) = v2{acc[2], acc[3]};
                 }
             }
         }
     };
-    for (int tile = blockIdx.x; tile < ntiles; tile += 2 * G) {
-        process(tile, xrA, hrA, tile + 2 * G);
-        if (tile + G < ntiles) process(tile + G, xrB, hrB, tile + 3 * G);
+    if constexpr (TWO) {
+        for (int tile = blockIdx.x; tile < ntiles; tile += 2 * G) {
+            process(tile, xrA, hrA, tile + 2 * G);
+            if (tile + G < ntiles) process(tile + G, xrB, hrB, tile + 3 * G);
+        }
+    } else {
+        for (int tile = blockIdx.x; tile < ntiles; tile += G) process(tile, xrA, hrA, tile + G);
     }
 }
 
@@ -890,7 +920,7 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_h64(FlowArgs single, 
 // tile and keeps that hidden tile's gate and U_h fragments in registers for
 // the whole launch (90 VGPRs at K = 3, H = 128: the FP8 weights that BF16
 // could not keep resident); the MLP fragments live in LDS.  Products are
-// formed transposed (weights x activations^T) as in k_net_h64, so a lane
+// formed transposed (weights x activations^T) as in k_net_reg, so a lane
 // holds one patch row and four consecutive units; the per-patch row maxima
 // of the quantised activations are reduced over lanes and then over the
 // waves of the row through LDS.
@@ -1212,8 +1242,8 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
     }
 }
 
-// Persistent BF16 kernel on 128-patch tiles for the shapes k_net_h64 does not
-// cover (H = 128, or K = 3), Hm = 0 or H.  Eight waves; wave w owns hidden
+// Persistent BF16 kernel on 128-patch tiles for the shapes k_net_reg does not
+// cover (H = 128, or H = 64 at K = 3), Hm = 0 or H.  Eight waves; wave w owns hidden
 // tile w % HT for the 8 / (8 / HT) row tiles of its row group, so each weight
 // fragment streamed from L2 (the weights, 368 KB at K = 3, H = 128, fit
 // neither in registers nor in LDS) feeds 8 (H = 128) or 4 (H = 64) row tiles
@@ -1544,18 +1574,22 @@ static bool standard_rows(const NetArgs &net)
     const int n = 1 << net.K;
     return net.nin == 4 * (n + 1) * (n + 1) + 4 && !net.reset_after;
 }
-static bool use_h64(int prec, int K, int H, int Hm) { return prec == 1 && H == 64 && K <= 2 && (Hm == 0 || Hm == 64); }
-static bool use_h64(const NetArgs &net) { return standard_rows(net) && use_h64(net.prec, net.K, net.H, net.Hm); }
+// (H = 96 at K = 3 and other MLP widths run the streamed kernel)
+static bool use_reg(const NetArgs &net)
+{
+    return net.prec == 1 && net.K <= 2 && net.H <= 96 && (net.Hm == 0 || net.Hm == net.H) &&
+           (net.nin == 40 || net.nin == 56 || net.nin == 104);
+}
 static bool use_q8p(const NetArgs &net)
 {
     return standard_rows(net) && net.prec == 2 && (net.H == 64 || net.H == 128) && (net.Hm == 0 || net.Hm == net.H);
 }
 static bool use_b16w(const NetArgs &net)
 {
-    return standard_rows(net) && net.prec == 1 && !use_h64(net) && (net.H == 64 || net.H == 128) &&
+    return standard_rows(net) && net.prec == 1 && !use_reg(net) && (net.H == 64 || net.H == 128) &&
            (net.Hm == 0 || net.Hm == net.H);
 }
-static bool persistent(const NetArgs &net) { return use_h64(net) || use_q8p(net) || use_b16w(net); }
+static bool persistent(const NetArgs &net) { return use_reg(net) || use_q8p(net) || use_b16w(net); }
 
 
 int net_blocks(const NetArgs &net, int row_tiles)
@@ -1567,7 +1601,9 @@ int net_blocks(const NetArgs &net, int row_tiles)
             if (hipDeviceGetAttribute(&g_num_cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
                 g_num_cus = 256;
         }
-        return row_tiles < g_num_cus ? row_tiles : g_num_cus;
+        // (at H = 32 a workgroup is four waves of up to 210 registers: two per CU)
+        const int most = use_reg(net) && net.H == 32 ? 2 * g_num_cus : g_num_cus;
+        return row_tiles < most ? row_tiles : most;
     }
     return row_tiles;
 }
@@ -1586,10 +1622,17 @@ static hipError_t launch_net_t(const FlowArgs &f, const BatchTable *bt, int nblo
 hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net, hipStream_t s)
 {
     const int nblocks = net_blocks(net, ntiles);
-    if (use_h64(net)) {
-        if (net.K == 1) hipLaunchKernelGGL(k_net_h64<1>, dim3(nblocks), dim3(kNetH64Threads), 0, s, f, bt, net, ntiles);
-        else hipLaunchKernelGGL(k_net_h64<2>, dim3(nblocks), dim3(kNetH64Threads), 0, s, f, bt, net, ntiles);
-        return hipGetLastError();
+    if (use_reg(net)) {
+#define DNNMG_REG(NN, HH)                                                                                              \
+        if (net.nin == NN && net.H == HH) {                                                                            \
+            hipLaunchKernelGGL((k_net_reg<NN, HH>), dim3(nblocks), dim3(net_reg_threads<HH>()), 0, s, f, bt, net, ntiles); \
+            return hipGetLastError();                                                                                  \
+        }
+        DNNMG_REG(40, 32) DNNMG_REG(56, 32) DNNMG_REG(104, 32)
+        DNNMG_REG(40, 64) DNNMG_REG(56, 64) DNNMG_REG(104, 64)
+        DNNMG_REG(40, 96) DNNMG_REG(56, 96) DNNMG_REG(104, 96)
+#undef DNNMG_REG
+        return hipErrorInvalidValue;
     }
     if (use_b16w(net)) {
         // 128-patch tiles: half as many blocks are enough

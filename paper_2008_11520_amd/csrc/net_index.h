@@ -59,7 +59,7 @@ DNNMG_HD inline int wide_h_row(int r, int na, int nb, int &half)
     return min(r & 63, (half ? nb : na) - 1);
 }
 
-// Predicate of the register prefetch of a 64-patch tile (k_net_h64,
+// Predicate of the register prefetch of a 64-patch tile (k_net_reg,
 // k_net_q8p): piece c of per_row pieces per row is read when it lies in the
 // tile (c < 64 per_row) and in one of its nrows rows; other pieces are zero.
 DNNMG_HD inline bool tile_piece_in(int c, int per_row, int nrows)
