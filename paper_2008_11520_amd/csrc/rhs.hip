@@ -33,6 +33,31 @@ __device__ inline bool dirichlet_node(unsigned dir, int I, int J, int NX, int NY
     return ((dir & 1u) && I == 0) || ((dir & 2u) && I == NX) || ((dir & 4u) && J == 0) || ((dir & 8u) && J == NY);
 }
 
+// Reciprocal in FP64: the hardware estimate and two Newton steps (a relative
+// error of a few 2^-53; the operand is a Jacobian determinant, positive and far
+// from the range's ends).
+__device__ __forceinline__ double rcp64(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+
+// x of the lane whose index differs in bit OFF (OFF = 1, 2: inside a group of
+// four lanes, a register move; else through LDS).
+template <int OFF>
+__device__ __forceinline__ double lane_xor(double x)
+{
+    if constexpr (OFF <= 2) {
+        constexpr int perm = OFF == 1 ? 0xB1 : 0x4E;   // quad_perm [1,0,3,2] and [2,3,0,1]
+        const int lo = __double2loint(x), hi = __double2hiint(x);
+        return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, perm, 0xF, 0xF, true),
+                                __builtin_amdgcn_mov_dpp(lo, perm, 0xF, 0xF, true));
+    } else {
+        return __shfl_xor(x, OFF);
+    }
+}
+
 // The explicit transport term of the theta scheme at the four corners c of
 // each patch E, in FP64:
 //   T_c = int_E N_c (u . grad u) + nu grad N_c . grad u  dx,  u = P v + d,
@@ -40,21 +65,43 @@ __device__ inline bool dirichlet_node(unsigned dir, int I, int J, int NX, int NY
 // restriction R = P^T of the fine rows T(u) is this integral of the coarse
 // hats, taken with the fine elements' 2 x 2 Gauss rule (u is bilinear on each
 // fine element, the map F bilinear on E).  Per Gauss point (xi, eta) in E's
-// reference square, with Cof = det J^{-T} and w = 1 / (4 n^2):
-//   w [ N_c (u_x (Cof grad_ref u)_x + u_y (Cof grad_ref u)_y)
-//       + (nu / det) (Cof grad_ref N_c) . (Cof grad_ref u) ].
+// reference square, with u_s, u_t the derivatives there, x_s, x_t, y_s, y_t the map's
+// and w = 1 / (4 n^2):
+//   w [ N_c cv + N_c,s a_s + N_c,t a_t ],
+//   cv = U u_s + V u_t,  U = u_x y_t - u_y x_t,  V = u_y x_s - u_x y_s,
+//   a_s = G11 u_s + G12 u_t,  a_t = G12 u_s + G22 u_t,
+//   (G11, G12, G22) = (nu / det) (x_t^2 + y_t^2, -(x_s x_t + y_s y_t), x_s^2 + y_s^2).
+// At fixed eta the hats are affine in xi and their xi-derivatives constant, so a row
+// of points needs the sums of cv, xi cv, a_s, a_t and xi a_t alone; they meet the hats
+// once per row.  About 60 FP64 instructions per point against 137 with the hats
+// and gradients formed at each, so 1024 x 256 patches at K = 2 take 73 us, not 100,
+// for the whole kernel (the averaging alone 41 us, HBM; FP64 issue about 40 us, of
+// which three waves per SIMD hide a part; at four waves it spills: 107 us).
 // One item per (patch, fine element row); the rows of a patch sit on
-// neighbouring lanes and are summed with a fixed butterfly.
+// neighbouring lanes and are summed with a fixed butterfly.  map: the first
+// item's map vectors (load_map64, clamped into the mesh), requested with the
+// tile's other loads.
+template <int K>
+__device__ __forceinline__ void load_map64(const FlowArgs &f, int it, int pi0, int pj0, double2 (&m)[3])
+{
+    constexpr int n = 1 << K, TP = kRhsFine / n;
+    const int pl = min(it / n, TP * TP - 1);
+    const int pi = min(pi0 + pl % TP, f.nx - 1), pj = min(pj0 + pl / TP, f.ny - 1);
+    const double2 *src = reinterpret_cast<const double2 *>(f.map64) + 4 * ((size_t)pj * f.nx + pi);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m[k] = src[k];
+}
+
 template <int K>
 __device__ __forceinline__ void transport_corners(const FlowArgs &f, int tid, int pi0, int pj0, const float2 *s_v,
-                                                  const float2 *s_dbar, double *s_T)
+                                                  const float2 *s_dbar, double *s_T, const double2 (&map)[3])
 {
     constexpr int n = 1 << K;
     constexpr int TP = kRhsFine / n, NO = kRhsFine + 1;
     constexpr int NI = TP * TP * n;
     static_assert(kThreads % n == 0, "a patch's rows on neighbouring lanes of one wave");
-    constexpr double inv_n = 1.0 / n, wq = 0.25 / (n * n);
-    constexpr double g0 = 0.21132486540518711775, g1 = 0.78867513459481288225;
+    constexpr double inv_n = 1.0 / n, wq = 0.25 / n;   // (the weight, times n)
+    constexpr double gp[2] = {0.21132486540518711775, 0.78867513459481288225};
     const double nu = f.nu64;
     const int nx = f.nx, ny = f.ny;
     for (int it0 = 0; it0 < NI; it0 += kThreads) {
@@ -63,67 +110,111 @@ __device__ __forceinline__ void transport_corners(const FlowArgs &f, int tid, in
         const int pa = pl % TP, pb = pl / TP;
         double acc[4][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
         if (it < NI && pi0 + pa < nx && pj0 + pb < ny) {
-            const double *m = f.map64 + 8 * ((size_t)(pj0 + pb) * nx + pi0 + pa);
-            const double exx = m[0], exy = m[1], eyx = m[2], eyy = m[3], twx = m[4], twy = m[5];
+            double2 m[3] = {map[0], map[1], map[2]};
+            if (it0 > 0) load_map64<K>(f, it, pi0, pj0, m);
+            const double exx = m[0].x, exy = m[0].y, eyx = m[1].x, eyy = m[1].y, twx = m[2].x, twy = m[2].y;
             constexpr int SV = TP + 2;     // the rhs tile's corner layout
             const int c = pb * SV + pa;
             const float2 v00 = s_v[c], v10 = s_v[c + 1], v01 = s_v[c + SV], v11 = s_v[c + SV + 1];
-            // u = P v + d at fine node (a, bb) of the patch, FP64
-            auto unode = [&](int a, int bb, double &ux, double &uy) {
-                const double xi = a * inv_n, eta = bb * inv_n;
-                const double n00 = (1.0 - xi) * (1.0 - eta), n10 = xi * (1.0 - eta), n01 = (1.0 - xi) * eta,
-                             n11 = xi * eta;
-                const float2 d = s_dbar[(pb * n + bb) * NO + pa * n + a];
-                ux = n00 * v00.x + n10 * v10.x + n01 * v01.x + n11 * v11.x + (double)d.x;
-                uy = n00 * v00.y + n10 * v10.y + n01 * v01.y + n11 * v11.y + (double)d.y;
-            };
-            double u0x, u0y, u2x, u2y;     // left column of the current element: rows b, b + 1
-            unode(0, b, u0x, u0y);
-            unode(0, b + 1, u2x, u2y);
-#pragma unroll 1
-            for (int a = 0; a < n; ++a) {
-                double u1x, u1y, u3x, u3y;
-                unode(a + 1, b, u1x, u1y);
-                unode(a + 1, b + 1, u3x, u3y);
-#pragma unroll 1
-                for (int q = 0; q < 4; ++q) {
-                        const double s = (q & 1) ? g1 : g0, t = (q >> 1) ? g1 : g0;
-                        const double xi = (a + s) * inv_n, eta = (b + t) * inv_n;
-                        const double xs = exx + twx * eta, ys = exy + twy * eta;
-                        const double xt = eyx + twx * xi, yt = eyy + twy * xi;
-                        const double det = xs * yt - xt * ys;
-                        const double ux = (1.0 - t) * (u0x + (u1x - u0x) * s) + t * (u2x + (u3x - u2x) * s);
-                        const double uy = (1.0 - t) * (u0y + (u1y - u0y) * s) + t * (u2y + (u3y - u2y) * s);
-                        // coarse-reference derivatives (n times the fine element's)
-                        const double usx = n * ((u1x - u0x) * (1.0 - t) + (u3x - u2x) * t);
-                        const double usy = n * ((u1y - u0y) * (1.0 - t) + (u3y - u2y) * t);
-                        const double utx = n * ((u2x - u0x) * (1.0 - s) + (u3x - u1x) * s);
-                        const double uty = n * ((u2y - u0y) * (1.0 - s) + (u3y - u1y) * s);
-                        // Cof grad_ref of each component
-                        const double gxx = yt * usx - ys * utx, gxy = -xt * usx + xs * utx;
-                        const double gyx = yt * usy - ys * uty, gyy = -xt * usy + xs * uty;
-                        const double cvx = ux * gxx + uy * gxy, cvy = ux * gyx + uy * gyy;
-                        const double nud = nu / det;
-                        const double N[4] = {(1.0 - xi) * (1.0 - eta), xi * (1.0 - eta), (1.0 - xi) * eta, xi * eta};
-                        const double Ns[4] = {-(1.0 - eta), 1.0 - eta, -eta, eta};
-                        const double Nt[4] = {-(1.0 - xi), -xi, 1.0 - xi, xi};
+            // P v on the node rows b and b + 1: left end and step per node
+            double pl0[2], ps0[2], pl1[2], ps1[2];
+            {
+                const double e0 = b * inv_n, e1 = (b + 1) * inv_n;
+                const double l[2] = {v00.x, v00.y}, r[2] = {v10.x, v10.y};
+                const double tl[2] = {v01.x, v01.y}, tr[2] = {v11.x, v11.y};
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const double hx = yt * Ns[k] - ys * Nt[k], hy = -xt * Ns[k] + xs * Nt[k];
-                            acc[k][0] += wq * (N[k] * cvx + nud * (hx * gxx + hy * gxy));
-                            acc[k][1] += wq * (N[k] * cvy + nud * (hx * gyx + hy * gyy));
+                for (int k = 0; k < 2; ++k) {
+                    const double dl = tl[k] - l[k], dr = tr[k] - r[k];
+                    pl0[k] = l[k] + dl * e0;
+                    pl1[k] = l[k] + dl * e1;
+                    ps0[k] = (r[k] + dr * e0 - pl0[k]) * inv_n;
+                    ps1[k] = (r[k] + dr * e1 - pl1[k]) * inv_n;
+                }
+            }
+            // u on node row b and u's step to row b + 1 at node column a, FP64
+            const float2 *const dr0 = s_dbar + (pb * n + b) * NO + pa * n;
+            auto column = [&](int a, double (&w)[2], double (&e)[2]) {
+                const float2 d0 = dr0[a], d1 = dr0[NO + a];
+                const double x = a;
+                w[0] = pl0[0] + ps0[0] * x + (double)d0.x;
+                w[1] = pl0[1] + ps0[1] * x + (double)d0.y;
+                e[0] = pl1[0] + ps1[0] * x + (double)d1.x - w[0];
+                e[1] = pl1[1] + ps1[1] * x + (double)d1.y - w[1];
+            };
+            // per row t of Gauss points: eta, x_s and y_s, det and its step in xi, G22 det
+            double xs[2], ys[2], dt0[2], dt1[2], g22[2], eta[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                eta[t] = (b + gp[t]) * inv_n;
+                xs[t] = exx + twx * eta[t];
+                ys[t] = exy + twy * eta[t];
+                dt0[t] = xs[t] * eyy - eyx * ys[t];
+                dt1[t] = xs[t] * twy - twx * ys[t];
+                g22[t] = xs[t] * xs[t] + ys[t] * ys[t];
+            }
+            // sums over the row's points [t][component], with the derivatives of u
+            // in the fine element's units (1 / n of E's) and without nu: both
+            // factors join at the end
+            double A0[2][2] = {}, A1[2][2] = {}, S0[2][2] = {}, T0[2][2] = {}, T1[2][2] = {};
+            double w0[2], e0[2];
+            column(0, w0, e0);
+            double xi0 = gp[0] * inv_n;
+#pragma unroll 1
+            for (int a = 0; a < n; ++a, xi0 += inv_n) {
+                double w1[2], e1[2];
+                column(a + 1, w1, e1);
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const double xi = s ? xi0 + (gp[1] - gp[0]) * inv_n : xi0;
+                    const double xt = eyx + twx * xi, yt = eyy + twy * xi, g11 = xt * xt + yt * yt;
+                    // u_t at s (the same for both t)
+                    const double ut[2] = {e0[0] + (e1[0] - e0[0]) * gp[s], e0[1] + (e1[1] - e0[1]) * gp[s]};
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const double l0 = w0[0] + e0[0] * gp[t], l1 = w0[1] + e0[1] * gp[t];
+                        const double us[2] = {w1[0] + e1[0] * gp[t] - l0, w1[1] + e1[1] * gp[t] - l1};
+                        const double ux = l0 + us[0] * gp[s], uy = l1 + us[1] * gp[s];
+                        const double rd = rcp64(dt0[t] + dt1[t] * xi);
+                        const double G11 = g11 * rd, G12 = -(xt * xs[t] + yt * ys[t]) * rd, G22 = g22[t] * rd;
+                        const double U = ux * yt - uy * xt, V = uy * xs[t] - ux * ys[t];
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            const double cv = U * us[k] + V * ut[k];
+                            const double at = G12 * us[k] + G22 * ut[k];
+                            A0[t][k] += cv;
+                            A1[t][k] += xi * cv;
+                            S0[t][k] += G11 * us[k];
+                            S0[t][k] += G12 * ut[k];
+                            T0[t][k] += at;
+                            T1[t][k] += xi * at;
                         }
                     }
-                u0x = u1x; u0y = u1y; u2x = u3x; u2y = u3y;
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) { w0[k] = w1[k]; e0[k] = e1[k]; }
             }
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    // right-hand and left-hand hats' share of the row, times (1 - eta) and eta
+                    const double r = A1[t][k] + nu * S0[t][k], l = A0[t][k] - r;
+                    const double tr = nu * T1[t][k], tl = nu * T0[t][k] - tr;
+                    acc[0][k] += wq * ((1.0 - eta[t]) * l - tl);
+                    acc[1][k] += wq * ((1.0 - eta[t]) * r - tr);
+                    acc[2][k] += wq * (eta[t] * l + tl);
+                    acc[3][k] += wq * (eta[t] * r + tr);
+                }
         }
         // sum over the patch's n rows (lanes it - b .. it - b + n - 1)
 #pragma unroll
-        for (int off = 1; off < n; off <<= 1)
+        for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) acc[k][c] += __shfl_xor(acc[k][c], off);
+            for (int c = 0; c < 2; ++c) {
+                acc[k][c] += lane_xor<1>(acc[k][c]);
+                if constexpr (n >= 4) acc[k][c] += lane_xor<2>(acc[k][c]);
+                if constexpr (n >= 8) acc[k][c] += lane_xor<4>(acc[k][c]);
+            }
         if (it < NI && b == 0)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -213,6 +304,8 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
     const double2 *gt = reinterpret_cast<const double2 *>(f.geo64) + 2 * pt0;
     float2 v_r[VIT];
     double2 g_r[GIT];
+    double2 map_r[3];
+    if constexpr (CN) load_map64<K>(f, tid, pi0, pj0, map_r);
 #pragma unroll
     for (int i = 0; i < VIT; ++i) {
         const int t = min(tid + i * kThreads, NV - 1);
@@ -532,7 +625,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
     }
     __syncthreads();
     if constexpr (CN) {
-        transport_corners<K>(f, tid, pi0, pj0, s_v, s_dbar, s_T);
+        transport_corners<K>(f, tid, pi0, pj0, s_v, s_dbar, s_T, map_r);
         __syncthreads();
     }
     const double th_old = CN ? 1.0 - (double)f.theta : 0.0;
