@@ -173,18 +173,63 @@ int blocks_for(int kind, int nx, int ny, int K)
 constexpr int kFusedLDA = 104 + 64 + 16;       // [x | h | 8 zeros] rows (168 + 8 values), padded so that 16 rows of a fragment read fall in distinct LDS banks
 constexpr int kFusedLDH = 64 + 8;
 
-template <int HM, bool FRAME>
+//
+// NTH = 512 (small grids, see defect_small): two waves per hidden tile, each
+// for two row tiles, and everything the network reads from memory is requested
+// before the defect's element residuals (PRE): state and corner velocities into
+// registers, the weight fragments (fused_weights) into LDS.
+template <int RT> struct FusedPre {
+    f4 hp[RT];
+    float2 vc;
+};
+
+// The fragments of [W | U], U_h, M1 and M2 (or M) in LDS, 1 KB each, in the order and at
+// the offsets of the packed arrays; copied by the workgroup's second four
+// waves, which hold no strip, without passing through registers.
+constexpr int kFusedW1 = 3 * 4 * 6, kFusedW2 = 4 * 2;            // fragments of B1, and of B2, B3, B4 each
+template <int HM> constexpr int fused_weight_frags() { return kFusedW1 + (HM > 0 ? 3 : 2) * kFusedW2; }
+template <int HM>
+__device__ __forceinline__ void fused_weights(const NetArgs &net, int tid, bf8 *sW)
+{
+    typedef __attribute__((address_space(1))) void gvoid;
+    typedef __attribute__((address_space(3))) void lvoid;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    if (wave < 4) return;
+    constexpr int NF = fused_weight_frags<HM>();
+    static_assert(NF % 4 == 0 && kFusedW1 % 4 == 0 && kFusedW2 % 4 == 0, "whole rounds of four waves");
+#pragma unroll 4
+    for (int i = 0; i < NF / 4; ++i) {
+        const int fr = 4 * i + (wave - 4);
+        const bf8 *src;
+        if (fr < kFusedW1) src = reinterpret_cast<const bf8 *>(net.B1) + 64 * fr;
+        else if (fr < kFusedW1 + kFusedW2) src = reinterpret_cast<const bf8 *>(net.B2) + 64 * (fr - kFusedW1);
+        else if (fr < kFusedW1 + 2 * kFusedW2) src = reinterpret_cast<const bf8 *>(net.B3) + 64 * (fr - kFusedW1 - kFusedW2);
+        else src = reinterpret_cast<const bf8 *>(net.B4) + 64 * (fr - kFusedW1 - 2 * kFusedW2);
+        __builtin_amdgcn_global_load_lds((gvoid *)(src + lane), (lvoid *)(sW + 64 * fr), 16, 0, 0);
+    }
+}
+
+template <bool LDS>
+__device__ inline auto fused_fragments(const void *p, const bf8 *sW)
+{
+    if constexpr (LDS) return sW;
+    else return pinned<bf8>(p);
+}
+
+template <int HM, bool FRAME, int NTH, bool PRE, int RT>
 __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int tid, const NetArgs &net,
                                           __bf16 *sA, __bf16 *sR, __bf16 *sHp, __bf16 *sAm, float *s_of,
-                                          float2 *s_vc)
+                                          float2 *s_vc, const bf8 *sW, FusedPre<RT> *pre, bool load_only)
 {
-    constexpr int nin = 104, nout = 50, H = 64, KC = 32, KQ = 8, KC1 = 6, TP = 8, RT = 4, HT = 4;
+    constexpr int nin = 104, nout = 50, H = 64, KC = 32, KQ = 8, KC1 = 6, TP = 8, HT = 4;
+    static_assert(RT * NTH == 4 * kThreads, "the waves cover the tile's four row tiles");
     constexpr int LDA = kFusedLDA, LDH = kFusedLDH;
     static_assert((nin + H) % KQ == 0 && nin + H > (KC1 - 1) * KC, "k-padding only in the last chunk");
     static_assert(LDA >= nin + H + KQ, "room for the zeros after [x | h]");
     const int nx = f.nx, ny = f.ny;
     const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lq = lane >> 4;
-    const int ht = wave, ucol = 16 * ht + 4 * lq;
+    const int ht = NTH > kThreads ? wave & 3 : wave, ucol = 16 * ht + 4 * lq;
+    const int rt0 = NTH > kThreads ? RT * (wave >> 2) : 0;      // first row tile of this wave
     auto valid = [&](int r) { return tx * TP + r % TP < nx && ty * TP + r / TP < ny; };
     // This lane's rows 16 q + li are patches (2 q + li / 8, li % 8) of the
     // tile: their state and outputs are addressed from the tile's first patch
@@ -196,31 +241,47 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
     const unsigned roff = ((li >> 3) ? (unsigned)nx : 0u) + (unsigned)(li & 7);
     auto patch = [&](int r) { return (size_t)(ty * TP + r / TP) * nx + tx * TP + r % TP; };
     auto hrow = [&](int q) {
-        return FRAME ? f.h + p00 * H + (roff + 2u * q * (unsigned)nx) * H + ucol : f.h + patch(16 * q + li) * H + ucol;
+        return FRAME ? f.h + p00 * H + (roff + 2u * (rt0 + q) * (unsigned)nx) * H + ucol
+                     : f.h + patch(16 * (rt0 + q) + li) * H + ucol;
     };
-    const gptr<bf8> B1 = pinned<bf8>(net.B1);
-    const gptr<bf8> B2 = pinned<bf8>(net.B2);
-    const gptr<bf8> B3 = pinned<bf8>(net.B3);
-    const gptr<bf8> B4 = pinned<bf8>(net.B4);
+    const auto B1 = fused_fragments<PRE>(net.B1, sW);
+    const auto B2 = fused_fragments<PRE>(net.B2, sW + 64 * kFusedW1);
+    const auto B3 = fused_fragments<PRE>(net.B3, sW + 64 * (kFusedW1 + kFusedW2));
+    const auto B4 = fused_fragments<PRE>(net.B4, sW + 64 * (kFusedW1 + 2 * kFusedW2));
     // the tile's state in this lane's layout (rows 16 q + li, units ucol..+3):
     // one HBM read serves the MFMA operand (BF16, next to the network input)
     // and the update.  It is waited for only after the k-chunks that hold
     // input alone.
     f4 hp[RT];
+    auto load_hp = [&](f4 (&o)[RT]) {
 #pragma unroll
-    for (int q = 0; q < RT; ++q) {
-        const int r = 16 * q + li;
-        hp[q] = valid(r) ? *reinterpret_cast<const f4 *>(hrow(q)) : f4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int q = 0; q < RT; ++q) {
+            const int r = 16 * (rt0 + q) + li;
+            o[q] = valid(r) ? *reinterpret_cast<const f4 *>(hrow(q)) : f4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
     // corner velocities of the tile's patches, for the averaging after the
     // network when the outputs stay in LDS (f.frame); loaded on every launch,
     // clamped into the mesh, and stored once the input-only chunks are issued
     constexpr int SVF = TP + 1;
     float2 vc = make_float2(0.f, 0.f);
-    if constexpr (FRAME) {
+    auto load_vc = [&]() {
         const int t = min(tid, SVF * SVF - 1);
         const int ci = min(t % SVF, nx - tx * TP), cj = min(t / SVF, ny - ty * TP);
-        vc = reinterpret_cast<const float2 *>(f.v)[(size_t)(ty * TP + cj) * (nx + 1) + tx * TP + ci];
+        return reinterpret_cast<const float2 *>(f.v)[(size_t)(ty * TP + cj) * (nx + 1) + tx * TP + ci];
+    };
+    if constexpr (PRE) {
+        if (load_only) {
+            load_hp(pre->hp);
+            if constexpr (FRAME) pre->vc = load_vc();
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < RT; ++q) hp[q] = pre->hp[q];
+        vc = pre->vc;
+    } else {
+        load_hp(hp);
+        if constexpr (FRAME) vc = load_vc();
     }
     // zeros after [x | h]: the lanes of the last k-chunk that lie beyond it
     // read these (the zero is formed from tile_thread(), so that it is not
@@ -242,7 +303,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
         const int kk = last && k0 >= nin + H ? nin + H : k0;
 #pragma unroll
         for (int q = 0; q < RT; ++q) {
-            const bf8 a = *reinterpret_cast<const bf8 *>(&sA[(16 * q + li) * LDA + kk]);
+            const bf8 a = *reinterpret_cast<const bf8 *>(&sA[(16 * (rt0 + q) + li) * LDA + kk]);
             const f4 z0 = {0.f, 0.f, 0.f, 0.f};
             az[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wz, a, first ? z0 : az[q], 0, 0, 0);
             ar[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr, a, first ? z0 : ar[q], 0, 0, 0);
@@ -260,12 +321,17 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
     for (int q = 0; q < RT; ++q) {
         bf4 hb;
         hb[0] = (__bf16)hp[q].x; hb[1] = (__bf16)hp[q].y; hb[2] = (__bf16)hp[q].z; hb[3] = (__bf16)hp[q].w;
-        *reinterpret_cast<bf4 *>(&sA[(16 * q + li) * LDA + nin + ucol]) = hb;
+        *reinterpret_cast<bf4 *>(&sA[(16 * (rt0 + q) + li) * LDA + nin + ucol]) = hb;
     }
     if (FRAME && f.frame && tid < SVF * SVF) s_vc[tid] = vc;
     __syncthreads();
+    if constexpr (PRE) {
+#pragma unroll
+        for (int kc = KX; kc < KC1 - 1; ++kc) chunk(kc, false, false);
+    } else {
 #pragma unroll 1
-    for (int kc = KX; kc < KC1 - 1; ++kc) chunk(kc, false, false);
+        for (int kc = KX; kc < KC1 - 1; ++kc) chunk(kc, false, false);
+    }
     chunk(KC1 - 1, false, true);
     bf8 w2[2];
 #pragma unroll
@@ -274,7 +340,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
     __syncthreads();   // every wave is done with the input rows (r*h reuses them)
 #pragma unroll
     for (int q = 0; q < RT; ++q) {
-        const int r = 16 * q + li;
+        const int r = 16 * (rt0 + q) + li;
         bf4 rh;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -288,7 +354,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
     // ---- phase 2: U_h (r*h); new state
 #pragma unroll
     for (int q = 0; q < RT; ++q) {
-        const int r = 16 * q + li;
+        const int r = 16 * (rt0 + q) + li;
         f4 au = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kc = 0; kc < 2; ++kc)
@@ -317,7 +383,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
         for (int kc = 0; kc < 2; ++kc) w3[kc] = B3[(ht * 2 + kc) * 64 + lane];
 #pragma unroll
         for (int q = 0; q < RT; ++q) {
-            const int r = 16 * q + li;
+            const int r = 16 * (rt0 + q) + li;
             f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kc = 0; kc < 2; ++kc)
@@ -338,7 +404,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
     f4 acc[RT];
 #pragma unroll
     for (int q = 0; q < RT; ++q) {
-        const int r = 16 * q + li;
+        const int r = 16 * (rt0 + q) + li;
         acc[q] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kc = 0; kc < 2; ++kc)
@@ -353,7 +419,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
     }
 #pragma unroll
     for (int q = 0; q < RT; ++q) {
-        const int r = 16 * q + li;
+        const int r = 16 * (rt0 + q) + li;
         // nout is even: the pairs (ucol, ucol+1), (ucol+2, ucol+3) are inside or outside together
         if (frame) {
             float *o = s_of + r * nout + ucol;
@@ -361,7 +427,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
             if (ucol + 2 < nout) *reinterpret_cast<float2 *>(o + 2) = make_float2(acc[q][2], acc[q][3]);
         }
         if ((!frame || f.keep_dpatch) && valid(r)) {
-            float *o = FRAME ? f.dpatch + p00 * nout + (roff + 2u * q * (unsigned)nx) * nout + ucol
+            float *o = FRAME ? f.dpatch + p00 * nout + (roff + 2u * (rt0 + q) * (unsigned)nx) * nout + ucol
                              : f.dpatch + patch(r) * nout + ucol;
             if (ucol < nout) *reinterpret_cast<float2 *>(o) = make_float2(acc[q][0], acc[q][1]);
             if (ucol + 2 < nout) *reinterpret_cast<float2 *>(o + 2) = make_float2(acc[q][2], acc[q][3]);
@@ -381,6 +447,7 @@ __device__ __forceinline__ void gru_fused(const FlowArgs &f, int tx, int ty, int
 // + 1)^2 nodes: u at deep nodes, d at inner ones) and then stored row by row
 // with 16-byte stores: stored node by node straight from the sums, the 8-byte
 // values of one store instruction would lie 32 bytes apart.
+template <int NTH>
 __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty, int tid, const float2 *s_o,
                                               const float2 *s_vc, float2 *s_img)
 {
@@ -401,7 +468,7 @@ __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty,
     static_assert(kThreads == 4 * 64 && FR::SIDE <= 64, "one side per wave");
     {
         const int w = tid >> 6, l = tid & 63;
-        if (l < FR::SIDE) {
+        if ((NTH == kThreads || w < 4) && l < FR::SIDE) {
             int pa, pb, a, b;
             FR::side_pos(w, l, pa, pb, a, b);
             if (pi0 + pa < nx && pj0 + pb < ny) fr[w * FR::SIDE + l] = s_o[(pb * TP + pa) * nf + b * (n + 1) + a];
@@ -427,7 +494,10 @@ __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty,
     // order, are those of the rhs kernel.
     const bool chk = f.nonfinite != nullptr;
     {
-        const int pl = tid % (TP * TP), b = tid / (TP * TP);
+        // (small grids: two threads per node row, two nodes each)
+        constexpr int NA = n * kThreads / NTH;
+        const int a0 = NTH == kThreads ? 0 : (tid >> 8) * NA;
+        const int pl = tid % (TP * TP), b = (tid / (TP * TP)) % n;
         const int pa = pl % TP, pb = pl / TP, pi = pi0 + pa, pj = pj0 + pb;
         const int lj = pb * n + b;
         if (pi < nx && pj < ny && lj > 0) {
@@ -440,7 +510,8 @@ __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty,
             const float2 *const ql = s_o + (low ? pl - TP : pl) * nf + n * (n + 1);   // top row of the patch below
             const float2 z = make_float2(0.f, 0.f);
 #pragma unroll
-            for (int a = 0; a < n; ++a) {
+            for (int aa = 0; aa < NA; ++aa) {
+                const int a = a0 + aa;
                 const int li = pa * n + a;
                 if (a == 0 && pa == 0) continue;                               // li = 0: boundary line
                 float2 acc = z;
@@ -472,8 +543,9 @@ __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty,
     // the mesh end inside a ragged tile: its last node column li = le and row
     // lj = me (on a full tile these are boundary lines)
     const int le = min(TP, nx - pi0) * n, me = min(TP, ny - pj0) * n;
-    if (tid < le + me + 1) {
-        const int li = tid <= me ? le : tid - me - 1, lj = tid <= me ? tid : me;
+    const int tl = NTH == kThreads ? tid : tid - kThreads;      // (threads that hold no node row, where there are some)
+    if (tl >= 0 && tl < le + me + 1) {
+        const int li = tl <= me ? le : tl - me - 1, lj = tl <= me ? tl : me;
         if (frame_kind(li, lj) != kFrameEdge) {
             const int I = I0 + li, J = J0 + lj;
             const int pI = min(I >> K, nx - 1), pJ = min(J >> K, ny - 1);
@@ -507,7 +579,7 @@ __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty,
     constexpr int DL = kTileFine - 3, PR = (DL + 1) / 2;   // deep nodes per row, stores per row
     static_assert(DL % 2 == 1, "pairs, then one node");
     const int lim = NX - I0, ljm = NY - J0;                // last tile node inside the mesh
-    for (int t = tid; t < DL * PR; t += kThreads) {
+    for (int t = tid; t < DL * PR; t += NTH) {
         const int lj = 2 + t / PR, c = t - (t / PR) * PR, li = 2 + 2 * c;
         if (lj > ljm || li > lim) continue;
         const float2 a = s_img[lj * NO + li];
@@ -539,7 +611,12 @@ __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty,
 // the patch nodes, momentum rows (D) then continuity rows, the corner
 // velocities, Peclet numbers and twelve geometry values, padded with zeros to
 // a multiple of 8 values.
-template <int K, typename XT, bool OPAQUE_TID, bool FUSED = false, int HM = 0, bool CN = false, bool PAPER = false>
+// NTH = 512 (small grids): the halo elements run on waves of their own beside
+// the strips (K = 1: each wave takes half the strips), the first-step flag is
+// not waited for before the state is requested, and the fused network's operands
+// are requested before the defect.
+template <int K, typename XT, bool OPAQUE_TID, bool FUSED = false, int HM = 0, bool CN = false, bool PAPER = false,
+          int NTH = kThreads>
 __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const NetArgs *net = nullptr)
 {
     static_assert(!(CN && FUSED), "the theta scheme runs unfused");
@@ -573,16 +650,18 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
     const int tx = blk % tiles_x, ty = blk / tiles_x;
     const int ci0 = tx * TP - 1, cj0 = ty * TP - 1;   // first (halo) coarse element
     const int I0 = tx * kTileFine, J0 = ty * kTileFine;
+    constexpr bool SMALL = NTH > kThreads;
+    static_assert(!SMALL || (NTH == 2 * kThreads && !OPAQUE_TID), "small-grid tiles: 512 threads, one tile per block");
     const int first = *f.first_flag;
     const float inv_dt = f.inv_dt, nu = f.nu;
 
     // 0. the previous corrected velocity on the tile's nodes + halo: issue the
     //    loads now, use them after the coarse records are formed
     //    (node t of the halo grid is row t / NN, column t % NN; thread tid
-    //    takes t = tid + i kThreads, stepped by kThreads = DR rows + DC
+    //    takes t = tid + i NTH, stepped by NTH = DR rows + DC
     //    columns, with a 32-bit offset from the grid's first node)
-    constexpr int NIT = (NN * NN + kThreads - 1) / kThreads;
-    constexpr int DR = kThreads / NN, DC = kThreads % NN;
+    constexpr int NIT = (NN * NN + NTH - 1) / NTH;
+    constexpr int DR = NTH / NN, DC = NTH % NN;
     float2 uq[NIT];
     if constexpr (OPAQUE_TID) {
         // (batched: the index form that keeps fewer registers live)
@@ -600,9 +679,10 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
         unsigned off = (unsigned)row * (unsigned)up + (unsigned)col;
 #pragma unroll
         for (int i = 0; i < NIT; ++i) {            // issue every load first
-            const int t = tid + i * kThreads;
+            const int t = tid + i * NTH;
             const int I = I0 - 1 + col, J = J0 - 1 + row;
-            const bool in = t < NN * NN && !first && I >= 0 && I <= NX && J >= 0 && J <= NY;
+            // (a small grid selects the first step's zeros when the values are used)
+            const bool in = t < NN * NN && (SMALL || !first) && I >= 0 && I <= NX && J >= 0 && J <= NY;
             uq[i] = in ? ub[off] : make_float2(0.f, 0.f);
             row += DR;
             col += DC;
@@ -623,7 +703,7 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
     const float2 *v2 = reinterpret_cast<const float2 *>(f.v);
     const bool has_p = f.p != nullptr;
     const float *p1 = has_p ? f.p : reinterpret_cast<const float *>(f.v);   // read and discarded without p
-    for (int t = tid; t < CE * CE; t += kThreads) {
+    for (int t = tid; t < CE * CE; t += NTH) {
         const int ci = min(max(ci0 + t % CE, 0), nx - 1), cj = min(max(cj0 + t / CE, 0), ny - 1);
         // (single flow: 32-bit offsets, 6 P and the corner count fit; the
         // batched form keeps the index form it was tuned with)
@@ -654,13 +734,25 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
     const bool theta_elems = CN && !first;
 #pragma unroll
     for (int i = 0; i < NIT; ++i) {
-        const int t = tid + i * kThreads;
+        const int t = tid + i * NTH;
         if (t >= NN * NN) break;
+        if (SMALL && first) uq[i] = make_float2(0.f, 0.f);
         const float sw = CN ? 1.0f : idt;
         s_w[t] = make_float2(uq[i].x * sw, uq[i].y * sw);
         s_acc[t] = make_float2(0.f, 0.f);
     }
     __syncthreads();
+
+    // (the fused network's operands: requested here, behind the defect's own
+    // loads, and waited for when the input rows are complete)
+    constexpr int RTF = 4 * kThreads / NTH;
+    FusedPre<RTF> pre;
+    __shared__ __align__(16) bf8 s_w8[FUSED && SMALL ? 64 * fused_weight_frags<HM>() : 1];
+    if constexpr (FUSED && SMALL) {
+        gru_fused<HM, true, NTH, true, RTF>(f, tx, ty, tid, *net, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, s_w8,
+                                            &pre, true);
+        fused_weights<HM>(*net, tid, s_w8);
+    }
 
     // 3. element residuals, kept in registers (the formulas are in
     //    element.h).  The tile's own elements are taken as vertical strips of
@@ -670,19 +762,25 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
     //    the tile, one per thread, is computed element by element.
     constexpr int SH = n < 4 ? n : 4;                      // strip height
     constexpr int NSR = kTileFine / SH;                    // strip rows per tile
-    constexpr int SPL = kTileFine * NSR / kThreads;        // strips per thread
-    static_assert(kTileFine == kTileElems && kThreads == 256 && NSR == 8 * SPL,
+    constexpr int SPT = kTileFine * NSR / kThreads;        // strips per lane of the four colours' waves
+    // strips per thread (the theta scheme's tiles keep the strips of K = 1 together:
+    // their rounding then is that of the 256-thread tiles, bit for bit)
+    constexpr int SPL = SMALL && SPT == 2 && !CN ? 1 : SPT;
+    static_assert(kTileFine == kTileElems && kThreads == 256 && NSR == 8 * SPT,
                   "strip mapping: 16 columns x 4 strip rows per wave and strip");
-    const int wave = tid >> 6, lane = tid & 63;
+    // (small grids: the second four waves take each colour's second strips, or
+    // hold no strip)
+    const int wave = SMALL ? (tid >> 6) & 3 : tid >> 6, lane = tid & 63;
+    const int half = SMALL ? tid >> 8 : 0;
     float S[SPL][SH + 1][4];
     int sn0[SPL];                                          // lower-left node of the strip (-1: outside the mesh)
 #pragma unroll
     for (int s = 0; s < SPL; ++s) {
         int ec, sr;
-        strip_of(wave, lane, s, ec, sr);
+        strip_of(wave, lane, SPL < SPT ? half : s, ec, sr);
         const int eI = I0 + ec, eJ = J0 + sr * SH;
         sn0[s] = -1;
-        if (eI < NX && eJ < NY) {
+        if (eI < NX && eJ < NY && (!SMALL || SPL < SPT || half == 0)) {
             const int n0 = (sr * SH + 1) * NN + ec + 1;
             sn0[s] = n0;
             const CoarseRec &r = s_c[((eJ >> K) - cj0) * CE + ((eI >> K) - ci0)];
@@ -710,9 +808,10 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
     constexpr int NH = 4 * (kTileFine + 1);
     float Rh[8];
     int hn0 = -1, hcol = -1;
-    if (tid < NH) {
+    const int th = SMALL ? NTH - 1 - tid : tid;            // (small grids: from the last wave down)
+    if (th < NH) {
         int le, me;                                        // tile-local element (-1 .. kTileFine)
-        halo_of(tid, le, me, hcol);
+        halo_of(th, le, me, hcol);
         const int eI = I0 + le, eJ = J0 + me;
         if (eI >= 0 && eI < NX && eJ >= 0 && eJ < NY) {
             const int n0 = (me + 1) * NN + le + 1;
@@ -760,19 +859,30 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
     constexpr int NO = kTileFine + 1;
     const bool masked = ((dir & 1u) && I0 == 0) || ((dir & 2u) && I0 + kTileFine >= NX) ||
                         ((dir & 4u) && J0 == 0) || ((dir & 8u) && J0 + kTileFine >= NY);
-    if (masked || f.D)
-    for (int t = tid; t < NO * NO; t += kThreads) {
-        const int li = t % NO, lj = t / NO;
-        const int I = I0 + li, J = J0 + lj;
-        if (I > NX || J > NY) continue;
-        const bool m = ((dir & 1u) && I == 0) || ((dir & 2u) && I == NX) || ((dir & 4u) && J == 0) ||
-                       ((dir & 8u) && J == NY);
-        float2 &d = s_acc[(lj + 1) * NN + li + 1];
-        if (m) d = make_float2(0.f, 0.f);
-        // stage entry: the defect itself, written by the tile that owns the node
-        if (f.D && (li < kTileFine || I == NX) && (lj < kTileFine || J == NY))
-            reinterpret_cast<float2 *>(f.D)[(size_t)J * (NX + 1) + I] = d;
+    auto masked_node = [&](int I, int J) {
+        return ((dir & 1u) && I == 0) || ((dir & 2u) && I == NX) || ((dir & 4u) && J == 0) || ((dir & 8u) && J == NY);
+    };
+    if (masked) {
+        // (masked nodes of a tile lie on its first node column and row and on
+        // the mesh's last ones)
+        for (int t = tid; t < 4 * NO; t += NTH) {
+            const int side = t / NO, m = t - side * NO;
+            const int li = side == 0 ? 0 : (side == 1 ? min(NX - I0, kTileFine) : m);
+            const int lj = side == 2 ? 0 : (side == 3 ? min(NY - J0, kTileFine) : m);
+            if (I0 + li <= NX && J0 + lj <= NY && masked_node(I0 + li, J0 + lj))
+                s_acc[(lj + 1) * NN + li + 1] = make_float2(0.f, 0.f);
+        }
+        if (f.D) __syncthreads();
     }
+    // stage entry: the defect itself, written by the tile that owns the node
+    if (f.D)
+        for (int t = tid; t < NO * NO; t += NTH) {
+            const int li = t % NO, lj = t / NO;
+            const int I = I0 + li, J = J0 + lj;
+            if (I > NX || J > NY) continue;
+            if ((li < kTileFine || I == NX) && (lj < kTileFine || J == NY))
+                reinterpret_cast<float2 *>(f.D)[(size_t)J * (NX + 1) + I] = s_acc[(lj + 1) * NN + li + 1];
+        }
     if (!FUSED && !f.X) return;
     __syncthreads();
 
@@ -784,10 +894,10 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
         // convert and write byte pairs into rows of xstride bytes (zero
         // beyond nin).
         uint8_t *s_q = reinterpret_cast<uint8_t *>(s_wx);
-        constexpr int G = kThreads / (TP * TP);            // lanes per patch: 1, 4 or 16
+        constexpr int G = NTH / (TP * TP);                 // lanes per patch: 1, 4 or 16 (twice that on small grids)
         constexpr int NI = (nf + 1 + G - 1) / G;           // items (node or features) per lane
         constexpr bool KEEP = NI <= 8;
-        static_assert(G * TP * TP == kThreads && (G & (G - 1)) == 0 && G <= 64, "patch lane groups");
+        static_assert(G * TP * TP == NTH && (G & (G - 1)) == 0 && G <= 64, "patch lane groups");
         // item (patch pl, node l < nf): P v and D at the node; l == nf: the features
         auto node_values = [&](int pl, int l, float4 &o) {
             const int pa = pl % TP, pb = pl / TP;
@@ -844,7 +954,7 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
         }
         __syncthreads();
         constexpr int CPR = TP * XS8 / 16;                 // 16-byte pieces per tile row of patches
-        for (int t = tid; t < TP * CPR; t += kThreads) {
+        for (int t = tid; t < TP * CPR; t += NTH) {
             const int pb = t / CPR, c = t - pb * CPR;
             const int pj = ty * TP + pb;
             if (pj >= ny || c * 16 >= npr * XS8) continue;
@@ -899,7 +1009,7 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
             };
             const float inv_nu = 1.0f / f.nu;
             const float2 *vg = reinterpret_cast<const float2 *>(f.v);
-            for (int t = tid; t < PP * (n + 2); t += kThreads) {
+            for (int t = tid; t < PP * (n + 2); t += NTH) {
                 const bool extra = t >= PP * (n + 1);
                 const int pl = extra ? t - PP * (n + 1) : t / (n + 1), b = extra ? n + 1 : t - pl * (n + 1);
                 const int pa = pl % TP, pb = pl / TP, pi = tx * TP + pa, pj = ty * TP + pb;
@@ -937,7 +1047,7 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
         } else
         // (items of one patch on consecutive lanes: their LDS rows interleave
         // across the banks, where one row per lane would stride LDX apart)
-        for (int t = tid; t < PP * (n + 2); t += kThreads) {
+        for (int t = tid; t < PP * (n + 2); t += NTH) {
             const bool feat = t >= PP * (n + 1);
             const int pl = feat ? t - PP * (n + 1) : t / (n + 1), b = feat ? n + 1 : t - pl * (n + 1);
             const int pa = pl % TP, pb = pl / TP;
@@ -962,6 +1072,7 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
                 store2(o + 2 * nf + 2 * l, dd.x, dd.y);
             }
         }
+        if constexpr (FUSED && SMALL) __builtin_amdgcn_s_waitcnt(0);   // this wave's weight fragments are in LDS
         __syncthreads();
         if constexpr (FUSED) {
             // the network input rows stay in LDS; r*h, h' reuse them after phase
@@ -976,16 +1087,17 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
             // alike, so the frame code is always there; a flow without a tile
             // frame stores the per-patch outputs)
             constexpr bool FRAME = !OPAQUE_TID;
-            gru_fused<HM, FRAME>(f, tx, ty, tid, *net, sA, sA, sA + 64 * kFusedLDH,
-                                 reinterpret_cast<__bf16 *>(s_acc), reinterpret_cast<float *>(s_wx), s_vc);
+            gru_fused<HM, FRAME, NTH, SMALL, RTF>(f, tx, ty, tid, *net, sA, sA, sA + 64 * kFusedLDH,
+                                                  reinterpret_cast<__bf16 *>(s_acc), reinterpret_cast<float *>(s_wx),
+                                                  s_vc, s_w8, &pre, false);
             if (FRAME && f.frame) {
                 __syncthreads();
-                fused_average(f, tx, ty, tid, reinterpret_cast<const float2 *>(s_wx), s_vc, s_acc);
+                fused_average<NTH>(f, tx, ty, tid, reinterpret_cast<const float2 *>(s_wx), s_vc, s_acc);
             }
             return;
         }
         constexpr int CPR = TP * nin * sizeof(XT) / 16;   // 16-byte pieces per tile row of patches
-        for (int t = tid; t < TP * CPR; t += kThreads) {
+        for (int t = tid; t < TP * CPR; t += NTH) {
             const int pb = t / CPR, c = t - pb * CPR;
             const int pj = ty * TP + pb;
             if (pj >= ny || c * 16 >= npr * nin * (int)sizeof(XT)) continue;
@@ -1054,6 +1166,38 @@ __global__ __launch_bounds__(kThreads, 4) void k_defect_net(FlowArgs single, con
     defect_tile<2, __bf16, false, true, HM>(f, blk, &net);
 }
 
+// Tiles of 512 threads (see defect_tile, NTH).  On a grid of a few tiles per CU
+// 256-thread tiles leave one or two waves per SIMD: one wave issues a vector
+// instruction every 5 to 9 cycles (two or more together every 3) and waits alone
+// for every load.  Bound by that latency: the one-launch K = 2 step on 4 tiles
+// 15.3 -> 11.2 us, on 256 tiles 17.9 -> 13.2 us; K = 1, FP32, one tile 10.8 -> 6.7 us;
+// 301 x 83, K = 1, Crank-Nicolson, paper input 19.0 -> 14.6 us.  The fused kernel, whose
+// weights take 96 KB of LDS, runs one tile per CU and only where there are no
+// more (375 tiles: step 26.2 us with 256-thread tiles, 30.3 us).
+constexpr int kSmallThreads = 512;
+static bool defect_small(int ntiles, int per_cu)
+{
+    // (a constant of the machine, read once)
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        (void)hipGetDevice(&dev);
+        return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 256;
+    }();
+    return ntiles <= per_cu * cus;
+}
+
+template <int HM>
+__global__ __launch_bounds__(kSmallThreads, 2) void k_defect_net_small(FlowArgs single, NetArgs net)
+{
+    defect_tile<2, __bf16, false, true, HM, false, false, kSmallThreads>(single, xcd_tile(blockIdx.x, gridDim.x), &net);
+}
+
+template <int K, typename XT, bool CN, bool PAPER>
+__global__ __launch_bounds__(kSmallThreads, 2) void k_defect_small(FlowArgs single)
+{
+    defect_tile<K, XT, false, false, 0, CN, PAPER, kSmallThreads>(single, xcd_tile(blockIdx.x, gridDim.x));
+}
+
 bool fused_step(const NetArgs &net)
 {
     return net.prec == 1 && net.K == 2 && net.H == 64 && (net.Hm == 0 || net.Hm == 64) && net.xform == 0 &&
@@ -1064,6 +1208,11 @@ hipError_t launch_defect_net(const FlowArgs &f, const BatchTable *bt, int nblock
 {
     if (!fused_step(net) || f.theta != 1.0f) return hipErrorInvalidValue;
     dim3 g(nblocks), b(kThreads);
+    if (!bt && defect_small(nblocks, 1)) {
+        if (net.Hm == 64) hipLaunchKernelGGL((k_defect_net_small<64>), g, dim3(kSmallThreads), 0, s, f, net);
+        else hipLaunchKernelGGL((k_defect_net_small<0>), g, dim3(kSmallThreads), 0, s, f, net);
+        return hipGetLastError();
+    }
     if (net.Hm == 64) {
         if (bt) hipLaunchKernelGGL((k_defect_net<true, 64>), g, b, 0, s, f, bt, net);
         else hipLaunchKernelGGL((k_defect_net<false, 64>), g, b, 0, s, f, bt, net);
@@ -1074,36 +1223,50 @@ hipError_t launch_defect_net(const FlowArgs &f, const BatchTable *bt, int nblock
     return hipGetLastError();
 }
 
+// One input form.  512-thread tiles: always at K = 1 with FP32 or BF16 rows
+// (the tile's LDS leaves two or three workgroups per CU whatever their size: step
+// of 1024 x 256 patches, H = 32, FP32 118 -> 106 us, BF16 66 -> 61 us), else up to
+// two tiles per CU (K = 2, 100 x 60: FP32 37 -> 34 us, FP8 27.4 -> 25.4 us; at 300 x
+// 200, 1900 tiles, they would lose 1-2 %) and four at K = 1 with FP8 rows.
+template <int K, typename XT, bool PAPER>
+static void launch_defect_t(const FlowArgs &f, const BatchTable *bt, int nblocks, bool cn, hipStream_t s)
+{
+    constexpr bool ALWAYS = K == 1 && !std::is_same<XT, uint8_t>::value;
+    const dim3 g(nblocks), b(kThreads), bs(kSmallThreads);
+    if (bt) {
+        if constexpr (!PAPER) hipLaunchKernelGGL((k_defect<K, XT, true>), g, b, 0, s, f, bt);
+    } else if (ALWAYS || defect_small(nblocks, K == 1 ? 4 : 2)) {
+        if (cn) hipLaunchKernelGGL((k_defect_small<K, XT, true, PAPER>), g, bs, 0, s, f);
+        else hipLaunchKernelGGL((k_defect_small<K, XT, false, PAPER>), g, bs, 0, s, f);
+    } else if constexpr (!ALWAYS) {
+        if (cn) hipLaunchKernelGGL((k_defect_form<K, XT, true, PAPER>), g, b, 0, s, f);
+        else if constexpr (PAPER) hipLaunchKernelGGL((k_defect_form<K, XT, false, true>), g, b, 0, s, f);
+        else hipLaunchKernelGGL((k_defect<K, XT, false>), g, b, 0, s, f, bt);
+    }
+}
+
+template <int K>
+static void launch_defect_k(const FlowArgs &f, const BatchTable *bt, int nblocks, int xfmt, hipStream_t s)
+{
+    const bool cn = f.theta != 1.0f, paper = f.xform != 0;
+    if (paper && xfmt == 1) launch_defect_t<K, __bf16, true>(f, bt, nblocks, cn, s);
+    else if (paper) launch_defect_t<K, float, true>(f, bt, nblocks, cn, s);
+    else if (xfmt == 1) launch_defect_t<K, __bf16, false>(f, bt, nblocks, cn, s);
+    else if (xfmt == 2) launch_defect_t<K, uint8_t, false>(f, bt, nblocks, cn, s);
+    else launch_defect_t<K, float, false>(f, bt, nblocks, cn, s);
+}
+
 hipError_t launch_defect(const FlowArgs &f, const BatchTable *bt, int nblocks, int K, int xfmt, hipStream_t s)
 {
-    dim3 g(nblocks), b(kThreads);
     const bool cn = f.theta != 1.0f, paper = f.xform != 0;
     if ((cn || paper) && bt) return hipErrorInvalidValue;
     if (paper && (xfmt == 2 || !f.geo12)) return hipErrorInvalidValue;
-#define DNNMG_DEFECT_LAUNCH(KK, XT)                                                           \
-    if (bt) hipLaunchKernelGGL((k_defect<KK, XT, true>), g, b, 0, s, f, bt);                   \
-    else if (cn) hipLaunchKernelGGL((k_defect_form<KK, XT, true, false>), g, b, 0, s, f);      \
-    else hipLaunchKernelGGL((k_defect<KK, XT, false>), g, b, 0, s, f, bt);
-#define DNNMG_DEFECT_PAPER(KK, XT)                                                            \
-    if (cn) hipLaunchKernelGGL((k_defect_form<KK, XT, true, true>), g, b, 0, s, f);            \
-    else hipLaunchKernelGGL((k_defect_form<KK, XT, false, true>), g, b, 0, s, f);
-#define DNNMG_DEFECT_CASE(KK)                                                                 \
-    case KK:                                                                                  \
-        if (paper && xfmt == 1) { DNNMG_DEFECT_PAPER(KK, __bf16) }                            \
-        else if (paper) { DNNMG_DEFECT_PAPER(KK, float) }                                     \
-        else if (xfmt == 1) { DNNMG_DEFECT_LAUNCH(KK, __bf16) }                               \
-        else if (xfmt == 2) { DNNMG_DEFECT_LAUNCH(KK, uint8_t) }                              \
-        else { DNNMG_DEFECT_LAUNCH(KK, float) }                                               \
-        break;
     switch (K) {
-        DNNMG_DEFECT_CASE(1)
-        DNNMG_DEFECT_CASE(2)
-        DNNMG_DEFECT_CASE(3)
+    case 1: launch_defect_k<1>(f, bt, nblocks, xfmt, s); break;
+    case 2: launch_defect_k<2>(f, bt, nblocks, xfmt, s); break;
+    case 3: launch_defect_k<3>(f, bt, nblocks, xfmt, s); break;
     default: return hipErrorInvalidValue;
     }
-#undef DNNMG_DEFECT_CASE
-#undef DNNMG_DEFECT_PAPER
-#undef DNNMG_DEFECT_LAUNCH
     return hipGetLastError();
 }
 
