@@ -279,7 +279,9 @@ struct UMeshDev {
     float *rel = nullptr;
     double *dgeo = nullptr, *W = nullptr, *M4 = nullptr;
     int *cidx = nullptr;
-    float *feat = nullptr, *uprev = nullptr, *dloc = nullptr, *D = nullptr;
+    int *enb = nullptr, *vocc = nullptr;
+    unsigned *ecode = nullptr;
+    float *feat = nullptr, *uprev = nullptr, *dloc = nullptr;
     unsigned char *mask = nullptr;
 };
 
@@ -713,7 +715,9 @@ UArgs uargs(const dnnmg_ctx *c, const float *v, const float *p)
     u.first_flag = c->first_flag();
     u.uprev = m.uprev;
     u.dloc = m.dloc;
-    u.D = m.D;
+    u.enb = m.enb;
+    u.ecode = m.ecode;
+    u.vocc = m.vocc;
     u.X = c->X();
     u.dpatch = c->dpatch();
     u.part = c->part();
@@ -893,7 +897,9 @@ extern "C" int dnnmg_create_umesh(const dnnmg_config *cfg, const dnnmg_umesh *me
     const size_t o_W = take(sizeof(double) * m.W.size()), o_M4 = take(sizeof(double) * m.M4.size());
     const size_t o_dgeo = take(sizeof(double) * m.dgeo.size()), o_cidx = take(sizeof(int) * m.cidx.size());
     const size_t o_mask = take(m.mask.size()), o_up = take(sizeof(float) * 2 * (size_t)m.Fn);
-    const size_t o_dloc = take(sizeof(float) * 2 * (size_t)m.ne * m.nf), o_D = take(sizeof(float) * 2 * (size_t)m.Fn);
+    const size_t o_dloc = take(sizeof(float) * 2 * (size_t)m.ne * m.nf);
+    const size_t o_enb = take(sizeof(int) * m.enb.size()), o_ec = take(sizeof(unsigned) * m.ecode.size());
+    const size_t o_vocc = take(sizeof(int) * m.vocc.size());
     auto bail = [&](int code) {
         (void)hipFree(c->ws);
         (void)hipFree(d->dev);
@@ -913,7 +919,9 @@ extern "C" int dnnmg_create_umesh(const dnnmg_config *cfg, const dnnmg_umesh *me
     d->W = (double *)(d->dev + o_W); d->M4 = (double *)(d->dev + o_M4);
     d->dgeo = (double *)(d->dev + o_dgeo); d->cidx = (int *)(d->dev + o_cidx);
     d->mask = d->dev + o_mask; d->uprev = (float *)(d->dev + o_up);
-    d->dloc = (float *)(d->dev + o_dloc); d->D = (float *)(d->dev + o_D);
+    d->dloc = (float *)(d->dev + o_dloc);
+    d->enb = (int *)(d->dev + o_enb); d->ecode = (unsigned *)(d->dev + o_ec);
+    d->vocc = (int *)(d->dev + o_vocc);
     rc = build_weights(g, weights, st, &c->w);
     if (rc) { c->w = nullptr; return bail(rc); }
     hipError_t e = hipSuccess;
@@ -926,6 +934,9 @@ extern "C" int dnnmg_create_umesh(const dnnmg_config *cfg, const dnnmg_umesh *me
     up(d->node_occ, m.node_occ.data(), sizeof(int) * m.node_occ.size());
     up(d->cnode_ptr, m.cnode_ptr.data(), sizeof(int) * m.cnode_ptr.size());
     up(d->cnode_occ, m.cnode_occ.data(), sizeof(int) * m.cnode_occ.size());
+    up(d->enb, m.enb.data(), sizeof(int) * m.enb.size());
+    up(d->ecode, m.ecode.data(), sizeof(unsigned) * m.ecode.size());
+    up(d->vocc, m.vocc.data(), sizeof(int) * m.vocc.size());
     up(d->rel, m.rel32.data(), sizeof(float) * m.rel32.size());
     up(d->feat, m.feat.data(), sizeof(float) * m.feat.size());
     up(d->W, m.W.data(), sizeof(double) * m.W.size());
@@ -1118,8 +1129,7 @@ static int enqueue_ustep(dnnmg_ctx *c, const UArgs &u, hipStream_t st)
     if (ev) HIP_OR_FAIL(hipEventRecord(ev[1], st));
     HIP_OR_FAIL(launch_net(unet_args(c), nullptr, blocks_for(kKindNet, c->um->ne, 1, g.K), c->w->net, st));
     if (ev) HIP_OR_FAIL(hipEventRecord(ev[2], st));
-    HIP_OR_FAIL(launch_uaverage(u, st));            // D now holds the averaged correction
-    HIP_OR_FAIL(launch_urhs(u, c->um->D, st));
+    HIP_OR_FAIL(launch_urhs(u, nullptr, st));       // averages, stores the state and the correction
     if (ev) {
         HIP_OR_FAIL(hipEventRecord(ev[3], st));
         pr.steps++;

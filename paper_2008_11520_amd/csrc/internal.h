@@ -160,24 +160,26 @@ struct UArgs {
     const unsigned char *mask;       // Fn: Dirichlet nodes
     const int *node_ptr, *node_occ;  // Fn + 1, P nf
     const int *cnode_ptr, *cnode_occ;// Nc + 1, 4 P
+    const int *enb;                  // P x 4: the patch across each local edge, or -1
+    const unsigned *ecode;           // P: eight bits per edge and corner (umesh_build.h)
+    const int *vocc;                 // P x 4 x 4: the first gather-list entries of each corner
     int *first_flag;                 // nonzero before the first step (then u_prev := P v)
     float *uprev;                    // Fn x 2
     float *dloc;                     // P x nf x 2: each patch's element contributions to its nodes
-    float *D;                        // Fn x 2: the assembled defect, then (step) the averaged correction
     void *X;                         // P x nin network input (FP32 or BF16)
     const float *dpatch;             // P x nout
     double *part;                    // P x 4 x 2: the patches' rhs shares at their corners
     double *bL;                      // Nc x 2
     float *dbar_out;                 // optional Fn x 2
-    const float *dbar_in;            // stage: given correction
     float *pv_out, *pp_out;          // prolongation stage
     int *nonfinite;                  // non-finite check (or nullptr)
 };
 
 hipError_t launch_udefect(const UArgs &u, float *D_out, hipStream_t s);          // contributions, and D_out (if given)
 hipError_t launch_uinput(const UArgs &u, hipStream_t s);                         // network input rows
-hipError_t launch_uaverage(const UArgs &u, hipStream_t s);                       // averaging, state, correction
-hipError_t launch_urhs(const UArgs &u, const float *dbar, hipStream_t s);       // FP64 rhs shares per patch
+// FP64 rhs shares per patch: of the patches' averaged outputs, which it also
+// stores (state, correction), or of a given correction dbar (the state untouched).
+hipError_t launch_urhs(const UArgs &u, const float *dbar, hipStream_t s);
 hipError_t launch_ugather(const UArgs &u, hipStream_t s);                        // b_L at the coarse nodes
 hipError_t launch_uprolong(const UArgs &u, hipStream_t s);                       // P v, P p at the fine nodes
 

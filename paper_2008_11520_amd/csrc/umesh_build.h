@@ -6,6 +6,13 @@
 // with the FP64 reference implementation.
 #pragma once
 
+#ifdef __HIP__
+#include <hip/hip_runtime.h>
+#define DNNMG_UM_HD __host__ __device__
+#else
+#define DNNMG_UM_HD
+#endif
+
 #include <cmath>
 #include <cstdint>
 #include <string>
@@ -24,6 +31,15 @@ struct UMeshHost {
     std::vector<unsigned char> mask;    // Fn
     std::vector<int> node_ptr, node_occ;    // Fn + 1, ne nf (patch nf + l, patch order)
     std::vector<int> cnode_ptr, cnode_occ;  // nc + 1, 4 ne (patch 4 + corner)
+    // Neighbours across the element's local edges (v0,v1), (v1,v2), (v3,v2),
+    // (v0,v3): enb the patch there (-1: none); ecode, eight bits per edge, where its
+    // nodes lie in it (neighbour_node below), whether the edge is Dirichlet, and
+    // whether corner v_k (with edge k's bits) is.  vocc: per corner v_k the first
+    // four entries of its gather list (-1: the list is shorter); a corner with
+    // more patches has kLongList first.
+    std::vector<int> enb;               // ne x 4
+    std::vector<unsigned> ecode;        // ne
+    std::vector<int> vocc;              // ne x 4 x 4
     std::vector<float> feat;            // ne x 4: hx, hy, hx / hy, area
     // A patch with straight edges is the bilinear image of the reference
     // square, its fine elements those of the uniform sub-squares: its mass
@@ -38,6 +54,31 @@ struct UMeshHost {
     std::vector<double> W;              // (patches with a curved edge) x 4 x nf
     std::vector<double> M4;             // (patches with a curved edge) x 4 x 4
 };
+
+// Inner nodes of patch edges: node t (1 .. n - 1, counted along the local edge
+// from its first end) of local edge k is patch-local node edge_node(n, k, t); in
+// the neighbour across the edge it is edge_node(n, j, r ? n - t : t).  The code
+// holds r (bit 0), j (bits 1, 2) and Dirichlet flags (bit 3 the edge, bit 4 the corner).
+DNNMG_UM_HD inline int edge_node(int n, int k, int t)
+{
+    const int a = (k & 1) ? (k == 1 ? n : 0) : t, b = (k & 1) ? t : (k == 2 ? n : 0);
+    return b * (n + 1) + a;
+}
+DNNMG_UM_HD inline int neighbour_node(int n, unsigned code, int t)
+{
+    return edge_node(n, (int)(code >> 1) & 3, (code & 1u) ? n - t : t);
+}
+constexpr unsigned kEdgeDirichlet = 8u, kCornerDirichlet = 16u;
+constexpr int kLongList = -2;
+// The local edge of patch-local node (a, b) and the node's place t on it, for a
+// node inside an edge; -1 for one inside the patch, -2 for a corner.
+DNNMG_UM_HD inline int edge_of_node(int n, int a, int b, int &t)
+{
+    const bool ea = a == 0 || a == n, eb = b == 0 || b == n;
+    if (ea && eb) return -2;
+    t = eb ? a : b;
+    return eb ? (b == 0 ? 0 : 2) : (ea ? (a == n ? 1 : 3) : -1);
+}
 
 namespace umesh_detail {
 
@@ -221,6 +262,30 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
             }
         }
     }
+    // neighbours across the edges
+    m.enb.assign(4 * (size_t)ne, -1);
+    m.ecode.assign((size_t)ne, 0u);
+    {
+        std::vector<int> first((size_t)m.E, -1);
+        auto start = [&](int ek) {      // first end of local edge ek % 4 of element ek / 4
+            const int *v = elems + 4 * (size_t)(ek / 4);
+            const int k = ek % 4;
+            return k == 1 ? v[1] : (k == 2 ? v[3] : v[0]);
+        };
+        auto join = [&](int x, int y) {
+            const unsigned code = (unsigned)((y % 4) << 1) | (start(x) == start(y) ? 0u : 1u);
+            m.enb[x] = y / 4;
+            m.ecode[x / 4] |= code << (8 * (x % 4));
+        };
+        for (int x = 0; x < 4 * ne; ++x) {
+            int &f = first[eidx[x]];
+            if (f < 0) f = x;
+            else { join(x, f); join(f, x); }
+            const int *v = elems + 4 * (size_t)(x / 4);
+            const int ends[4][2] = {{v[0], v[1]}, {v[1], v[2]}, {v[3], v[2]}, {v[0], v[3]}};
+            if (dir.count(edge_key(ends[x % 4][0], ends[x % 4][1]))) m.ecode[x / 4] |= kEdgeDirichlet << (8 * (x % 4));
+        }
+    }
     // gather lists (counting sort keeps patch order)
     m.node_ptr.assign((size_t)m.Fn + 1, 0);
     for (int x : m.pmap) m.node_ptr[x + 1]++;
@@ -230,6 +295,13 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
         std::vector<int> at(m.node_ptr.begin(), m.node_ptr.end() - 1);
         for (int e = 0; e < ne; ++e)
             for (int l = 0; l < nf; ++l) m.node_occ[at[m.pmap[(size_t)e * nf + l]]++] = e * nf + l;
+    }
+    m.vocc.assign(16 * (size_t)ne, -1);
+    for (int x = 0; x < 4 * ne; ++x) {
+        const int f = elems[x], k0 = m.node_ptr[f], cnt = m.node_ptr[f + 1] - k0;
+        for (int k = 0; k < 4 && k < cnt; ++k) m.vocc[4 * (size_t)x + k] = m.node_occ[k0 + k];
+        if (cnt > 4) m.vocc[4 * (size_t)x] = kLongList;
+        if (m.mask[f]) m.ecode[x / 4] |= kCornerDirichlet << (8 * (x % 4));
     }
     m.cnode_ptr.assign((size_t)nc + 1, 0);
     for (int i = 0; i < 4 * ne; ++i) m.cnode_ptr[elems[i] + 1]++;
