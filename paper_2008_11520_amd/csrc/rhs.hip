@@ -253,9 +253,16 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
 
     // the staged per-patch outputs (step) and, once the node pass has read
     // them, the averaged correction (or u) at the tile's nodes share one buffer
-    constexpr int kStaged = FROM_PATCHES == 1 ? HP * HP * nf : 0;
-    __shared__ float2 s_buf[kStaged > NO * NO ? kStaged : NO * NO];
+    // ROWS (the step from patches, K >= 2): both u and d go to LDS and are stored
+    // row by row.  Stored from the node pass, the 8-byte values of one store
+    // instruction lie 8 n bytes apart: 1024 x 256 patches, K = 2, 41.3 -> 36.6 us; 64
+    // flows of 128 x 128, K = 3, whole step with d asked for 2201 -> 2013 us.  At K = 1 they are
+    // 16 bytes apart and the extra pass costs more (one tile 5.8 -> 6.5 us).
+    constexpr bool ROWS = FROM_PATCHES == 1 && K >= 2;
+    constexpr int kStaged = FROM_PATCHES == 1 ? HP * HP * nf : 0, kImages = (ROWS ? 2 : 1) * NO * NO;
+    __shared__ float2 s_buf[kStaged > kImages ? kStaged : kImages];
     float2 *const s_dbar = s_buf;
+    float2 *const s_other = s_buf + (ROWS ? NO * NO : 0);   // d, or u where s_dbar holds d
     __shared__ float2 s_v[SV * SV];
     __shared__ double s_A[4 * (n + 1)];
     __shared__ double s_M[3 * 4 * 4];
@@ -494,8 +501,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
                 float px, py;
                 pv_of(li, lj, px, py);
                 u = make_float2(px + d.x, py + d.y);
-                const bool owned = (li < kRhsFine || I == NX) && (lj < kRhsFine || J == NY);
-                if (owned) {
+                if (!ROWS && (li < kRhsFine || I == NX) && (lj < kRhsFine || J == NY)) {
                     ut[lj * up + li] = u;
                     if (f.dbar_out) (reinterpret_cast<float2 *>(f.dbar_out) + nt0)[lj * (NX + 1) + li] = d;
                 }
@@ -556,9 +562,9 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         // the corrections (or u) are kept in registers until every thread is
         // done reading the staged outputs, then written over them
         constexpr int OIT = (TP * TP * n + kThreads - 1) / kThreads;
-        float2 dreg[OIT][n];
+        float2 ureg[OIT][n], dreg[OIT][n];
         int dpos[OIT];
-        float2 dlast = make_float2(0.f, 0.f);
+        float2 dlast = make_float2(0.f, 0.f), ulast = dlast;
         int lpos = -1;
         // the nodes (a, b), a, b < n, of the tile's own patches, one node row of
         // one patch per item: the same sums as node() with the patch known
@@ -579,9 +585,6 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
             const int c = pb * SV + pa;
             const float2 v00 = s_v[c], v10 = s_v[c + 1], v01 = s_v[c + SV], v11 = s_v[c + SV + 1];
             const PvRow row = pv_row(v00.x, v00.y, v10.x, v10.y, v01.x, v01.y, v11.x, v11.y, b * inv_n);
-            float2 *const urow = ut + (pb * n + b) * up + pa * n;
-            float2 *const drow = f.dbar_out ? reinterpret_cast<float2 *>(f.dbar_out) + nt0 + (pb * n + b) * (NX + 1) + pa * n
-                                            : nullptr;
 #pragma unroll
             for (int a = 0; a < n; ++a) {
                 const bool lft = a == 0 && pi > 0;
@@ -596,10 +599,12 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
                 nonfin |= !(__builtin_isfinite(d.x) && __builtin_isfinite(d.y));
                 float px, py;
                 pv_at(row, a * inv_n, px, py);
-                const float2 u = make_float2(px + d.x, py + d.y);
-                urow[a] = u;
-                if (drow) drow[a] = d;
-                dreg[o][a] = UB ? u : d;
+                ureg[o][a] = make_float2(px + d.x, py + d.y);
+                dreg[o][a] = d;
+                if constexpr (!ROWS) {
+                    ut[(pb * n + b) * up + pa * n + a] = ureg[o][a];
+                    if (f.dbar_out) (reinterpret_cast<float2 *>(f.dbar_out) + nt0)[(pb * n + b) * (NX + 1) + pa * n + a] = d;
+                }
             }
         }
         // the rest: the last node column and row of the tile's patches (the
@@ -608,20 +613,54 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         static_assert(2 * kRhsFine + 1 <= kThreads, "one last-row/column node per thread");
         if (tid < le + me + 1) {
             const int li = tid <= me ? le : tid - me - 1, lj = tid <= me ? tid : me;
-            float2 u;
-            const float2 d = node(li, lj, u);
-            dlast = UB ? u : d;
+            dlast = node(li, lj, ulast);
             lpos = lj * NO + li;
         }
+        const bool both = ROWS && (!UB || f.dbar_out);
         __syncthreads();
 #pragma unroll
         for (int o = 0; o < OIT; ++o)
             if (dpos[o] >= 0) {
 #pragma unroll
-                for (int a = 0; a < n; ++a) s_dbar[dpos[o] + a] = dreg[o][a];
+                for (int a = 0; a < n; ++a) {
+                    s_dbar[dpos[o] + a] = UB ? ureg[o][a] : dreg[o][a];
+                    if (both) s_other[dpos[o] + a] = UB ? dreg[o][a] : ureg[o][a];
+                }
             }
-        if (lpos >= 0) s_dbar[lpos] = dlast;
+        if (lpos >= 0) {
+            s_dbar[lpos] = UB ? ulast : dlast;
+            if (both) s_other[lpos] = UB ? dlast : ulast;
+        }
         if (nonfin && f.nonfinite) atomicOr(f.nonfinite, 1);
+        if constexpr (ROWS) {
+        __syncthreads();
+        // the nodes that this tile owns (not its last column and row, unless
+        // the mesh ends there): a row of u in 16-byte stores (rows of the
+        // state start on 128-byte lines), a row of d node by node on
+        // neighbouring lanes (its rows are NX + 1 nodes)
+        const int cols = I0 + kRhsFine < NX ? kRhsFine : NX - I0 + 1, rows = J0 + kRhsFine < NY ? kRhsFine : NY - J0 + 1;
+        const float2 *const iu = UB ? s_dbar : s_other, *const id = UB ? s_other : s_dbar;
+        constexpr int PR = (NO + 1) / 2;
+        for (int t = tid; t < rows * PR; t += kThreads) {
+            const int lj = t / PR, li = 2 * (t - lj * PR);
+            if (li >= cols) continue;
+            const float2 x = iu[lj * NO + li];
+            float2 *const q = ut + lj * up + li;
+            if (li + 1 < cols) {
+                const float2 y = iu[lj * NO + li + 1];
+                *reinterpret_cast<float4 *>(q) = make_float4(x.x, x.y, y.x, y.y);
+            } else {
+                *q = x;
+            }
+        }
+        if (f.dbar_out) {
+            float2 *const dout = reinterpret_cast<float2 *>(f.dbar_out) + nt0;
+            for (int t = tid; t < rows * NO; t += kThreads) {
+                const int lj = t / NO, li = t - lj * NO;
+                if (li < cols) dout[lj * (NX + 1) + li] = id[lj * NO + li];
+            }
+        }
+        }
     }
     __syncthreads();
     if constexpr (CN) {
@@ -703,9 +742,9 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
 // Single flow: one tile per block.  Batched: the blocks stride over the
 // table's tiles of all flows, so the grid need not match the batch.
 // Waves per SIMD the rhs aims at (what its LDS allows; register budget 512 /
-// waves; the batched K = 3 instance needs more registers than 5 waves leave).
-template <int K, bool BATCHED>
-constexpr int rhs_waves() { return K == 2 ? 6 : (K == 3 && !BATCHED ? 5 : 4); }
+// waves; K = 3 needs more registers than 5 waves leave).
+template <int K>
+constexpr int rhs_waves() { return K == 2 ? 6 : 4; }
 
 // The theta scheme (Crank-Nicolson), single flow.
 template <int K, int FROM_PATCHES>
@@ -715,7 +754,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_rhs_cn(FlowArgs single, RhsTabl
 }
 
 template <int K, int FROM_PATCHES, bool BATCHED>
-__global__ __launch_bounds__(kThreads, (rhs_waves<K, BATCHED>())) void k_rhs(FlowArgs single, const BatchTable *__restrict__ bt, RhsTables tab)
+__global__ __launch_bounds__(kThreads, (rhs_waves<K>())) void k_rhs(FlowArgs single, const BatchTable *__restrict__ bt, RhsTables tab)
 {
     if constexpr (!BATCHED) {
         rhs_tile<K, FROM_PATCHES, false>(single, xcd_tile(blockIdx.x, gridDim.x), tab);
