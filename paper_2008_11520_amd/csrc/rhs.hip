@@ -574,7 +574,9 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         for (int o = 0; o < OIT; ++o) {
             const int it = tid + o * kThreads;
             dpos[o] = -1;
-            const int pl = it % (TP * TP), b = it / (TP * TP);
+            // (ROWS: a patch's node rows on neighbouring lanes, so that the 32 lanes
+            // of a tile-image store fall in distinct LDS banks)
+            const int pl = ROWS ? it / n : it % (TP * TP), b = ROWS ? it % n : it / (TP * TP);
             const int pa = pl % TP, pb = pl / TP, pi = pi0 + pa, pj = pj0 + pb;
             if (it >= TP * TP * n || pi >= nx || pj >= ny) continue;
             dpos[o] = (pb * n + b) * NO + pa * n;
@@ -744,7 +746,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
 // Waves per SIMD the rhs aims at (what its LDS allows; register budget 512 /
 // waves; K = 3 needs more registers than 5 waves leave).
 template <int K>
-constexpr int rhs_waves() { return K == 2 ? 6 : 4; }
+constexpr int rhs_waves() { return K == 2 ? 6 : (K == 3 ? 5 : 4); }
 
 // The theta scheme (Crank-Nicolson), single flow.
 template <int K, int FROM_PATCHES>
