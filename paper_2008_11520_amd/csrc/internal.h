@@ -201,10 +201,8 @@ bool fused_step(const NetArgs &net);
 hipError_t launch_defect_net(const FlowArgs &f, const BatchTable *bt, int nblocks, const NetArgs &net, hipStream_t s);
 // FP8 activation quantiser (stage entry point): rows x cols FP32 -> codes, scales.
 hipError_t launch_quantize(const float *a, int rows, int cols, uint8_t *q, float *s, hipStream_t st);
-hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int nblocks, const NetArgs &net,
+hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net,
                       hipStream_t s);
-// Blocks of the network launch (persistent kernels use fewer than row tiles).
-int net_blocks(const NetArgs &net, int row_tiles);
 // f.theta != 1 adds the explicit transport term -(1 - theta) R T(u) (single flow).
 hipError_t launch_rhs(const FlowArgs &f, const BatchTable *bt, int nblocks, int K,
                       const RhsTables &tab, int from_patches, hipStream_t s);

@@ -1584,28 +1584,38 @@ static bool use_q8p(const NetArgs &net)
 {
     return standard_rows(net) && net.prec == 2 && (net.H == 64 || net.H == 128) && (net.Hm == 0 || net.Hm == net.H);
 }
-static bool use_b16w(const NetArgs &net)
+static int num_cus()
 {
-    return standard_rows(net) && net.prec == 1 && !use_reg(net) && (net.H == 64 || net.H == 128) &&
-           (net.Hm == 0 || net.Hm == net.H);
-}
-static bool persistent(const NetArgs &net) { return use_reg(net) || use_q8p(net) || use_b16w(net); }
-
-
-int net_blocks(const NetArgs &net, int row_tiles)
-{
-    if (persistent(net)) {
-        if (g_num_cus == 0) {
-            int dev = 0;
-            (void)hipGetDevice(&dev);
-            if (hipDeviceGetAttribute(&g_num_cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-                g_num_cus = 256;
-        }
-        // (at H = 32 a workgroup is four waves of up to 210 registers: two per CU)
-        const int most = use_reg(net) && net.H == 32 ? 2 * g_num_cus : g_num_cus;
-        return row_tiles < most ? row_tiles : most;
+    if (g_num_cus == 0) {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        if (hipDeviceGetAttribute(&g_num_cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            g_num_cus = 256;
     }
-    return row_tiles;
+    return g_num_cus;
+}
+// The wide kernel keeps its weights in registers for all tiles of a block and
+// so pays for loading them first; with at most one row tile per CU there is no
+// second tile, and at H = 128 the streamed kernel, whose blocks start on their
+// rows at once, is the faster one.  Step times (us, wide against streamed) at
+// H = 128: K = 2, 60 patches 29.1 / 24.3, 8192 33.3 / 27.8, 15000 34.8 / 31.0,
+// 30000 (two tiles per CU) 39.4 / 41.6; K = 3, 60 patches 36.2 / 30.4, 8192
+// 43.9 / 38.9, 15000 52.5 / 48.3, 30000 73.4 / 80.7.  At H = 64 (K = 3) the two
+// are level up to one tile per CU (8192 patches 36.6 / 36.4), and the wide one
+// is kept.
+static bool use_b16w(const NetArgs &net, int row_tiles)
+{
+    if (!standard_rows(net) || net.prec != 1 || use_reg(net) || (net.Hm != 0 && net.Hm != net.H)) return false;
+    return net.H == 64 || (net.H == 128 && row_tiles > num_cus());
+}
+
+// Grid of a launch on row_tiles tiles: persistent kernels loop over them.
+static int net_blocks(const NetArgs &net, int row_tiles, bool persistent)
+{
+    if (!persistent) return row_tiles;
+    // (at H = 32 a workgroup is four waves of up to 210 registers: two per CU)
+    const int most = use_reg(net) && net.H == 32 ? 2 * num_cus() : num_cus();
+    return row_tiles < most ? row_tiles : most;
 }
 
 template <int PREC, int H>
@@ -1621,7 +1631,8 @@ static hipError_t launch_net_t(const FlowArgs &f, const BatchTable *bt, int nblo
 
 hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net, hipStream_t s)
 {
-    const int nblocks = net_blocks(net, ntiles);
+    const bool wide = use_b16w(net, ntiles);
+    const int nblocks = net_blocks(net, ntiles, use_reg(net) || use_q8p(net));
     if (use_reg(net)) {
 #define DNNMG_REG(NN, HH)                                                                                              \
         if (net.nin == NN && net.H == HH) {                                                                            \
@@ -1634,9 +1645,9 @@ hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const
 #undef DNNMG_REG
         return hipErrorInvalidValue;
     }
-    if (use_b16w(net)) {
+    if (wide) {
         // 128-patch tiles: half as many blocks are enough
-        dim3 g(net_blocks(net, (ntiles + 1) / 2)), b(kNetH64Threads);
+        dim3 g(net_blocks(net, (ntiles + 1) / 2, true)), b(kNetH64Threads);
 #define DNNMG_B16W(KK, HH, MM) hipLaunchKernelGGL((k_net_b16w<KK, HH, MM>), g, b, 0, s, f, bt, net, ntiles)
 #define DNNMG_B16W_H(KK)                                                                             \
         if (net.H == 64) { if (net.Hm == 64) DNNMG_B16W(KK, 64, 64); else DNNMG_B16W(KK, 64, 0); }    \
