@@ -643,7 +643,7 @@ __global__ __launch_bounds__(kThreads) void k_net_fp8(FlowArgs single, const Bat
 // streamed kernel, which holds two workgroups of six waves per CU and waits for
 // its rows at each tile's start, 126 us).  Any spill inside the loop waits for
 // the rows in flight (100 us with a second prefetch buffer at H = 96).
-constexpr int kNetH64Threads = 512;   // the persistent wide and FP8 kernels
+constexpr int kNetH64Threads = 512;   // the persistent wide kernel
 template <int H> constexpr int net_reg_threads() { return 8 * H; }
 
 template <int NIN, int H>
@@ -915,65 +915,113 @@ __global__ __launch_bounds__(net_reg_threads<H>(), (H == 96 ? 3 : 2)) void k_net
     }
 }
 
-// Persistent FP8 kernel (H = 64 or 128, Hm = 0 or H, K <= 3).  Eight waves:
-// wave w owns hidden tile w % HT for 4 / (8 / HT) row tiles of each 64-patch
-// tile and keeps that hidden tile's gate and U_h fragments in registers for
-// the whole launch (90 VGPRs at K = 3, H = 128: the FP8 weights that BF16
-// could not keep resident); the MLP fragments live in LDS.  Products are
-// formed transposed (weights x activations^T) as in k_net_reg, so a lane
-// holds one patch row and four consecutive units; the per-patch row maxima
-// of the quantised activations are reduced over lanes and then over the
+// Maximum over a group of lanes: the value of lane ^ 16, lane ^ 32 (swaps of
+// rows of 16 and of halves, which the vector unit does without LDS) ...
+__device__ inline float max_xor16(float m)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ inline float max_xor32(float m)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// ... and over a row of 16 lanes: quads by permutation, then the mirrored half rows and rows.
+template <int CTRL>
+__device__ inline float max_dpp(float m)
+{
+    return fmaxf(m, __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(m), CTRL, 0xF, 0xF, true)));
+}
+__device__ inline float max_row16(float m)
+{
+    return max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(m))));
+}
+
+// Persistent FP8 kernel (H = 64 or 128, Hm = 0 or H, K <= 3) on tiles of 32
+// patches.  One wave per hidden tile: it computes that tile for the tile's two
+// row tiles and keeps its gate and U_h fragments in registers for the whole
+// launch (90 VGPRs at K = 3, H = 128: the FP8 weights that BF16 could not keep
+// resident); the MLP fragments and the per-unit weight scales live in LDS.
+// Products are formed transposed (weights x activations^T) as in k_net_reg, so
+// a lane holds one patch row and four consecutive units; the per-patch row
+// maxima of the quantised activations are reduced over lanes and then over the
 // waves of the row through LDS.
+// Bound by the chain of a tile, seven barriers and six divisions per row, and
+// by the vector unit (830 instructions per wave and tile, as many as the
+// memory leaves time for): so the waves that wait for each other are few (four
+// at H = 64) and four workgroups of them share a CU.  At 1024 x 256 patches,
+// K = 2, H = 64: 70 us, 220 MB at 3.1 TB/s; with one workgroup of eight waves and
+// 64 patches per CU 92 us, with two of them 71.5 (113 with its registers
+// spilled: per-lane values are derived again in each tile, the state is read
+// twice).  On 50 x 30 patches at H = 128 the step went from 33.9 to 26.5 us.
+constexpr int kQ8Rows = 32;
+template <int H> constexpr int q8p_threads() { return 4 * H; }
+// Waves per SIMD that the registers allow: the resident weights take 22 to 48
+// VGPRs at K = 1 and 2, up to 90 at K = 3.
+constexpr int q8p_waves(int K) { return K <= 2 ? 4 : 2; }
+
 template <int K, int H, int HM>
-__global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, const BatchTable *__restrict__ bt,
+__global__ __launch_bounds__(q8p_threads<H>(), q8p_waves(K)) void k_net_q8p(FlowArgs single, const BatchTable *__restrict__ bt,
                                                                NetArgs net, int ntiles)
 {
     constexpr int n = 1 << K, nf = (n + 1) * (n + 1), nin = 4 * nf + 4, nout = 2 * nf;
     constexpr int KC = 32, KQ = 8;
     constexpr int XS = xstride_fp8(nin), KCX = XS / KC, HC = H / KC, KC1 = KCX + HC;
-    // wave w: hidden tile w % HT, row tiles RTW (w / HT) .. + RTW - 1 of a pass;
-    // a 64-patch tile takes PASSES passes (2 at H = 128, to bound registers)
-    constexpr int HT = H / 16, WPH = 8 / HT, RTW = 2, PASSES = 4 / (WPH * RTW);
+    constexpr int NT = q8p_threads<H>(), R = kQ8Rows;
+    constexpr int HT = H / 16, RTW = R / 16;             // wave w: hidden tile w of all the tile's rows
     constexpr int OT = (nout + 15) / 16;
     constexpr int MC = HM / KC;
     constexpr int LDX = XS + 16, LDQ = H + 16, LDS32 = H + 4;
     constexpr int W3N = (HM > 0 ? HM / 16 : OT) * HC * 64, W4N = HM > 0 ? OT * MC * 64 : 1;
     static_assert(HM == 0 || HM == H, "MLP hidden tiles follow the hidden tiles");
     if (bt) ntiles = bt->prefix[kKindNet][bt->nflows];   // batched: the table's row tiles
+    ntiles *= 64 / R;                                    // this kernel's tiles
 
-    __shared__ __align__(16) uint8_t sX[64 * LDX];       // network input codes of the tile
-    __shared__ __align__(16) float sH[64 * LDS32];       // FP32 state of the tile
-    __shared__ __align__(16) uint8_t sQ[64 * LDQ];       // state codes, then r*h codes
-    __shared__ __align__(16) uint8_t sHp[64 * LDQ];      // h' codes
-    __shared__ __align__(16) uint8_t sAm[64 * LDQ];      // MLP hidden codes
+    __shared__ __align__(16) uint8_t sX[R * LDX];       // network input codes of the tile
+    __shared__ __align__(16) float sH[R * LDS32];       // FP32 state of the tile
+    __shared__ __align__(16) uint8_t sQ[R * LDQ];       // state codes, then r*h codes
+    __shared__ __align__(16) uint8_t sHp[R * LDQ];      // h' codes
+    __shared__ __align__(16) uint8_t sAm[R * LDQ];      // MLP hidden codes
     __shared__ __align__(16) f8x8 sW3[W3N];
     __shared__ __align__(16) f8x8 sW4[W4N];
-    __shared__ float sMax[HT * 64];                     // per-wave partial row maxima
-    __shared__ float sSx[64], sSh[64];                  // row scales of x and h
+    __shared__ float sMax[HT * R];                     // per-wave partial row maxima
+    __shared__ __align__(16) float sRow[4 * R];          // row scales of x and h, their quotient
+    constexpr int SO = 3 * H + H + HM;                  // first output scale
+    __shared__ __align__(16) float sS[SO + 16 * OT];
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int li = lane & 15, lq = lane >> 4;
-    const int ht = wave % HT, rt0 = RTW * (wave / HT);   // row-tile offset within a pass
-    const int ucol = 16 * ht + 4 * lq;                  // first of this lane's four units
+    const int tid = threadIdx.x, ht = __builtin_amdgcn_readfirstlane(tid >> 6), lane0 = tid & 63;
     const f8x8 *B1 = reinterpret_cast<const f8x8 *>(net.B1);
     const f8x8 *B2 = reinterpret_cast<const f8x8 *>(net.B2);
     const f8x8 *B3 = reinterpret_cast<const f8x8 *>(net.B3);
     const f8x8 *B4 = reinterpret_cast<const f8x8 *>(net.B4);
 
-    f8x8 wz[KC1], wr[KC1], wh[KCX], w2[HC];
+    constexpr bool W2R = !(H == 128 && K == 2);          // U_h in registers (there it would spill), or in LDS
+    __shared__ __align__(16) f8x8 sW2[W2R ? 1 : HT * HC * 64];
+    f8x8 wz[KC1], wr[KC1], wh[KCX], w2[W2R ? HC : 1];
 #pragma unroll
     for (int kc = 0; kc < KC1; ++kc) {
-        wz[kc] = B1[((0 * HT + ht) * KC1 + kc) * 64 + lane];
-        wr[kc] = B1[((1 * HT + ht) * KC1 + kc) * 64 + lane];
+        wz[kc] = B1[((0 * HT + ht) * KC1 + kc) * 64 + lane0];
+        wr[kc] = B1[((1 * HT + ht) * KC1 + kc) * 64 + lane0];
     }
 #pragma unroll
-    for (int kc = 0; kc < KCX; ++kc) wh[kc] = B1[((2 * HT + ht) * KC1 + kc) * 64 + lane];
+    for (int kc = 0; kc < KCX; ++kc) wh[kc] = B1[((2 * HT + ht) * KC1 + kc) * 64 + lane0];
+    if constexpr (W2R) {
 #pragma unroll
-    for (int kc = 0; kc < HC; ++kc) w2[kc] = B2[(ht * HC + kc) * 64 + lane];
-    for (int t = tid; t < W3N; t += kNetH64Threads) sW3[t] = B3[t];
-    for (int t = tid; t < W4N; t += kNetH64Threads) sW4[t] = HM > 0 ? B4[t] : 0;
-    // per-unit weight scales: read where they are used (global, cached)
-    const gptr<float> S1 = pinned<float>(net.s1), S2 = pinned<float>(net.s2);
+        for (int kc = 0; kc < HC; ++kc) w2[kc] = B2[(ht * HC + kc) * 64 + lane0];
+    } else {
+        for (int t = tid; t < HT * HC * 64; t += NT) sW2[t] = B2[t];
+    }
+    for (int t = tid; t < W3N; t += NT) sW3[t] = B3[t];
+    for (int t = tid; t < W4N; t += NT) sW4[t] = HM > 0 ? B4[t] : 0;
+    // per-unit weight scales: z | r | candidate | U_h | M1 (or the output's) | output
+    for (int t = tid; t < 3 * H; t += NT) sS[t] = net.s1[t];
+    for (int t = tid; t < H; t += NT) sS[3 * H + t] = net.s2[t];
+    if (HM > 0)
+        for (int t = tid; t < H; t += NT) sS[4 * H + t] = net.s3[t];
+    for (int t = tid; t < 16 * OT; t += NT)
+        sS[SO + t] = t < nout ? (HM > 0 ? net.s4 : net.s3)[t] : 0.0f;
+    auto scales = [&](int at) { return *reinterpret_cast<const f4 *>(&sS[at]); };
 
     // A row tile's buffers.  The fields are read in two branches: a pointer
     // that may point at either the kernel argument or the batch table would
@@ -991,7 +1039,7 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
     float *const s_h = single.h, *const s_dp = single.dpatch;
     const int s_P = single.nx * single.ny;
     auto rows_of = [&](int tile) -> Rows {
-        int blk = tile;
+        int blk = tile / (64 / R);
         const void *X;
         const float *sxp;
         float *h, *dp;
@@ -1002,56 +1050,55 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
         } else {
             X = s_X; sxp = s_sx; h = s_h; dp = s_dp; P = s_P;
         }
-        const int row0 = blk * 64;
+        const int row0 = blk * 64 + R * (tile % (64 / R));
         Rows r;
         r.X = (gptr<uint8_t>)(reinterpret_cast<const uint8_t *>(X) + (size_t)row0 * XS);
         r.sx = (gptr<float>)(sxp + row0);
         r.h = (gfloat *)(h + (size_t)row0 * H);
         r.dp = (gfloat *)(dp + (size_t)row0 * nout);
-        r.nrows = min(64, P - row0);
+        r.nrows = min(R, P - row0);
         return r;
     };
 
     // next-tile prefetch into registers: network input codes, FP32 state, x
     // scales (index math from tile_thread(): recomputed in each tile instead
     // of hoisted out of the tile loop and held in registers)
-    constexpr int XCH = 64 * XS / 16, HCH = 64 * H / 4;
-    constexpr int XPT = (XCH + kNetH64Threads - 1) / kNetH64Threads;
-    constexpr int HPT = (HCH + kNetH64Threads - 1) / kNetH64Threads;
+    constexpr int XCH = R * XS / 16, HCH = R * H / 4;
+    constexpr int XPT = (XCH + NT - 1) / NT;
+    constexpr int HPT = (HCH + NT - 1) / NT;
     typedef unsigned int u4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(1))) const u4 gu4;
     typedef __attribute__((address_space(1))) const f4 gf4;
     u4 xr[XPT];
     f4 hr[HPT];
-    float sxr = 1.0f;
+    float sxr[HPT];                                     // x scale of the row of each state piece
     auto load_tile = [&](int tile) {
         const Rows rw = rows_of(tile);
         const int t0 = tile_thread();
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
-            const int c = t0 + i * kNetH64Threads;
+            const int c = t0 + i * NT;
             xr[i] = tile_piece_in(c, XS / 16, rw.nrows) ? ((gu4 *)rw.X)[c] : u4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
-            const int c = t0 + i * kNetH64Threads;
+            const int c = t0 + i * NT;
             hr[i] = tile_piece_in(c, H / 4, rw.nrows) ? ((gf4 *)rw.h)[c] : f4{0.f, 0.f, 0.f, 0.f};
+            sxr[i] = tile_piece_in(c, H / 4, rw.nrows) ? rw.sx[c / (H / 4)] : 1.0f;
         }
-        sxr = t0 < rw.nrows ? rw.sx[t0] : 1.0f;
     };
     if (blockIdx.x < ntiles) load_tile(blockIdx.x);
 
     // row maximum of |v| over the 16 units a wave holds for its row, then over
     // the HT waves of the row (the caller brackets this with barriers)
-    auto wave_max = [&](float m, int row) {
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        if (lq == 0) sMax[ht * 64 + row] = m;
+    auto wave_max = [&](float m, int row, int lq) {
+        m = max_xor32(max_xor16(m));
+        if (lq == 0) sMax[ht * R + row] = m;
     };
     auto row_max = [&](int row) {
         float m = kFp8MinMax;
 #pragma unroll
-        for (int t = 0; t < HT; ++t) m = fmaxf(m, sMax[t * 64 + row]);
+        for (int t = 0; t < HT; ++t) m = fmaxf(m, sMax[t * R + row]);
         return m;
     };
 
@@ -1061,42 +1108,45 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
         gfloat *const hg = rw.h;
         gfloat *const dp = rw.dp;
 
-        __syncthreads();   // the previous tile's readers of LDS are done
+        // (the rows staged here were last read before the previous tile's later barriers)
         const int t1 = tile_thread();
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
-            const int c = t1 + i * kNetH64Threads;
+            const int c = t1 + i * NT;
             if (c < XCH) *reinterpret_cast<u4 *>(&sX[(c / (XS / 16)) * LDX + 16 * (c % (XS / 16))]) = xr[i];
         }
         // the state: FP32 rows and their codes; the H / 4 consecutive threads
         // that hold one row's pieces reduce its maximum by shuffles
-        static_assert(HCH % kNetH64Threads == 0 && (H / 4) <= 64, "whole rows per pass");
+        static_assert(HCH % NT == 0 && (H / 4) <= 64, "whole rows per pass");
 #pragma unroll
         for (int i = 0; i < HPT; ++i) {
-            const int c = t1 + i * kNetH64Threads;
+            const int c = t1 + i * NT;
             const int row = c / (H / 4), k = 4 * (c % (H / 4));
             *reinterpret_cast<f4 *>(&sH[row * LDS32 + k]) = hr[i];
             float m = fmaxf(fmaxf(fabsf(hr[i].x), fabsf(hr[i].y)), fmaxf(fabsf(hr[i].z), fabsf(hr[i].w)));
-#pragma unroll
-            for (int o = 1; o < H / 4; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+            m = max_row16(m);
+            if constexpr (H == 128) m = max_xor16(m);
             m = fmaxf(m, kFp8MinMax);
             const float r = 448.0f / m;
-            if (k == 0) sSh[row] = m / 448.0f;
+            if (k == 0) {
+                const float sh = m / 448.0f;
+                *reinterpret_cast<f4 *>(&sRow[4 * row]) = f4{sxr[i], sh, sxr[i] / sh, 0.f};
+            }
             *reinterpret_cast<uint32_t *>(&sQ[row * LDQ + k]) =
                 pack4_e4m3(hr[i].x * r, hr[i].y * r, hr[i].z * r, hr[i].w * r);
         }
-        if (t1 < 64) sSx[t1] = sxr;
         if (tile + (int)gridDim.x < ntiles) load_tile(tile + gridDim.x);
         __syncthreads();
 
-        for (int pass = 0; pass < PASSES; ++pass) {
-            const int rtb = pass * WPH * RTW + rt0;      // first row tile of this wave in the pass
+        {
+            const int lane = tile_thread() & 63, li = lane & 15, lq = lane >> 4;
+            const int ucol = 16 * ht + 4 * lq;           // first of this lane's four units
             // ---- phase 1: the three gates of this wave's hidden tile
             f4 az[RTW], ar[RTW], ah[RTW];
             float sx[RTW], sh[RTW];
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
-                const int row = 16 * (rtb + q) + li;
+                const int row = 16 * q + li;
                 az[q] = ar[q] = ah[q] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kc = 0; kc < KCX; ++kc) {
@@ -1105,11 +1155,11 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
                     ar[q] = mma_fp8(ar[q], wr[kc], a);
                     ah[q] = mma_fp8(ah[q], wh[kc], a);
                 }
-                sx[q] = sSx[row];
-                sh[q] = sSh[row];
-                const float ratio = sx[q] / sh[q];
-                az[q] *= ratio;
-                ar[q] *= ratio;
+                const f4 rs = *reinterpret_cast<const f4 *>(&sRow[4 * row]);
+                sx[q] = rs.x;
+                sh[q] = rs.y;
+                az[q] *= rs.z;
+                ar[q] *= rs.z;
 #pragma unroll
                 for (int kh = 0; kh < HC; ++kh) {
                     const f8x8 a = mma_fp8_operand(&sQ[row * LDQ + kh * KC + lq * KQ]);
@@ -1117,26 +1167,26 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
                     ar[q] = mma_fp8(ar[q], wr[KCX + kh], a);
                 }
             }
-            f4 hold[RTW];
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
-                const int row = 16 * (rtb + q) + li;
-                hold[q] = *reinterpret_cast<const f4 *>(&sH[row * LDS32 + ucol]);
+                const int row = 16 * q + li;
+                const f4 hold = *reinterpret_cast<const f4 *>(&sH[row * LDS32 + ucol]);
+                const f4 sz = scales(ucol), sr = scales(H + ucol), sc = scales(2 * H + ucol);
                 float m = 0.0f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    az[q][e] = sigmoid(az[q][e] * sh[q] * S1[ucol + e]);
-                    ar[q][e] = sigmoid(ar[q][e] * sh[q] * S1[H + ucol + e]) * hold[q][e];   // r*h
-                    ah[q][e] *= sx[q] * S1[2 * H + ucol + e];
+                    az[q][e] = sigmoid(az[q][e] * sh[q] * sz[e]);
+                    ar[q][e] = sigmoid(ar[q][e] * sh[q] * sr[e]) * hold[e];   // r*h
+                    ah[q][e] *= sx[q] * sc[e];
                     m = fmaxf(m, fabsf(ar[q][e]));
                 }
-                wave_max(m, row);
+                wave_max(m, row, lq);
             }
             __syncthreads();
             float srh[RTW];
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
-                const int row = 16 * (rtb + q) + li;
+                const int row = 16 * q + li;
                 const float m = row_max(row), r = 448.0f / m;
                 srh[q] = m / 448.0f;
                 *reinterpret_cast<uint32_t *>(&sQ[row * LDQ + ucol]) =
@@ -1147,27 +1197,30 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
             // ---- phase 2: U_h (r*h); new state
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
-                const int row = 16 * (rtb + q) + li;
+                const int row = 16 * q + li;
                 f4 au = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kc = 0; kc < HC; ++kc) au = mma_fp8(au, w2[kc], mma_fp8_operand(&sQ[row * LDQ + kc * KC + lq * KQ]));
+                for (int kc = 0; kc < HC; ++kc) au = mma_fp8(au, W2R ? w2[W2R ? kc : 0] : sW2[W2R ? 0 : (ht * HC + kc) * 64 + lane],
+                                 mma_fp8_operand(&sQ[row * LDQ + kc * KC + lq * KQ]));
+                const f4 su = scales(3 * H + ucol);
+                const f4 hold = *reinterpret_cast<const f4 *>(&sH[row * LDS32 + ucol]);
                 float m = 0.0f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float z = az[q][e];
-                    const float c = fast_tanh(ah[q][e] + au[e] * srh[q] * S2[ucol + e]);
-                    const float hn = c + z * (hold[q][e] - c);   // z h + (1 - z) c
+                    const float c = fast_tanh(ah[q][e] + au[e] * srh[q] * su[e]);
+                    const float hn = c + z * (hold[e] - c);   // z h + (1 - z) c
                     az[q][e] = hn;
                     m = fmaxf(m, fabsf(hn));
                 }
                 if (row < nrows) *(__attribute__((address_space(1))) f4 *)(hg + row * H + ucol) = az[q];
-                wave_max(m, row);
+                wave_max(m, row, lq);
             }
             __syncthreads();
             float shp[RTW];
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
-                const int row = 16 * (rtb + q) + li;
+                const int row = 16 * q + li;
                 const float m = row_max(row), r = 448.0f / m;
                 shp[q] = m / 448.0f;
                 *reinterpret_cast<uint32_t *>(&sHp[row * LDQ + ucol]) =
@@ -1178,18 +1231,15 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
             // ---- MLP head
             const uint8_t *src = sHp;
             const f8x8 *Wo = sW3;
-            const float *so = net.s3;
             constexpr int CO = HM > 0 ? MC : HC;             // k-chunks of the output layer
             float sin_[RTW];
 #pragma unroll
             for (int q = 0; q < RTW; ++q) sin_[q] = shp[q];
             if constexpr (HM > 0) {
-                float s3u[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s3u[e] = net.s3[ucol + e];
+                const f4 s3u = scales(4 * H + ucol);
 #pragma unroll
                 for (int q = 0; q < RTW; ++q) {
-                    const int row = 16 * (rtb + q) + li;
+                    const int row = 16 * q + li;
                     f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int kc = 0; kc < HC; ++kc)
@@ -1200,12 +1250,12 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
                         ar[q][e] = fmaxf(acc[e] * shp[q] * s3u[e], 0.f);
                         m = fmaxf(m, ar[q][e]);
                     }
-                    wave_max(m, row);
+                    wave_max(m, row, lq);
                 }
                 __syncthreads();
 #pragma unroll
                 for (int q = 0; q < RTW; ++q) {
-                    const int row = 16 * (rtb + q) + li;
+                    const int row = 16 * q + li;
                     const float m = row_max(row), r = 448.0f / m;
                     sin_[q] = m / 448.0f;
                     *reinterpret_cast<uint32_t *>(&sAm[row * LDQ + ucol]) =
@@ -1214,16 +1264,13 @@ __global__ __launch_bounds__(kNetH64Threads, 2) void k_net_q8p(FlowArgs single, 
                 __syncthreads();
                 src = sAm;
                 Wo = sW4;
-                so = net.s4;
             }
             for (int ot = ht; ot < OT; ot += HT) {
                 const int oc = 16 * ot + 4 * lq;
-                float so4[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) so4[e] = oc + e < nout ? so[oc + e] : 0.0f;
+                const f4 so4 = scales(SO + oc);
 #pragma unroll
                 for (int q = 0; q < RTW; ++q) {
-                    const int row = 16 * (rtb + q) + li;
+                    const int row = 16 * q + li;
                     f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int kc = 0; kc < CO; ++kc)
@@ -1632,7 +1679,7 @@ static hipError_t launch_net_t(const FlowArgs &f, const BatchTable *bt, int nblo
 hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net, hipStream_t s)
 {
     const bool wide = use_b16w(net, ntiles);
-    const int nblocks = net_blocks(net, ntiles, use_reg(net) || use_q8p(net));
+    const int nblocks = net_blocks(net, ntiles, use_reg(net));
     if (use_reg(net)) {
 #define DNNMG_REG(NN, HH)                                                                                              \
         if (net.nin == NN && net.H == HH) {                                                                            \
@@ -1663,7 +1710,9 @@ hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const
         return hipGetLastError();
     }
     if (use_q8p(net)) {
-        dim3 g(nblocks), b(kNetH64Threads);
+        // as many workgroups of H / 16 waves as a CU's four SIMDs hold
+        const int most = 4 * q8p_waves(net.K) / (net.H / 16) * num_cus(), tiles = ntiles * (64 / kQ8Rows);
+        dim3 g(tiles < most ? tiles : most), b(4 * net.H);
 #define DNNMG_Q8P(KK, HH, MM) hipLaunchKernelGGL((k_net_q8p<KK, HH, MM>), g, b, 0, s, f, bt, net, ntiles)
 #define DNNMG_Q8P_H(KK)                                                                            \
         if (net.H == 64) { if (net.Hm == 64) DNNMG_Q8P(KK, 64, 64); else DNNMG_Q8P(KK, 64, 0); }    \
