@@ -643,7 +643,6 @@ __global__ __launch_bounds__(kThreads) void k_net_fp8(FlowArgs single, const Bat
 // streamed kernel, which holds two workgroups of six waves per CU and waits for
 // its rows at each tile's start, 126 us).  Any spill inside the loop waits for
 // the rows in flight (100 us with a second prefetch buffer at H = 96).
-constexpr int kNetH64Threads = 512;   // the persistent wide kernel
 template <int H> constexpr int net_reg_threads() { return 8 * H; }
 
 template <int NIN, int H>
@@ -1289,87 +1288,110 @@ __global__ __launch_bounds__(q8p_threads<H>(), q8p_waves(K)) void k_net_q8p(Flow
     }
 }
 
-// Persistent BF16 kernel on 128-patch tiles for the shapes k_net_reg does not
-// cover (H = 128, or H = 64 at K = 3), Hm = 0 or H.  Eight waves; wave w owns hidden
-// tile w % HT for the 8 / (8 / HT) row tiles of its row group, so each weight
-// fragment streamed from L2 (the weights, 368 KB at K = 3, H = 128, fit
-// neither in registers nor in LDS) feeds 8 (H = 128) or 4 (H = 64) row tiles
-// per gate.  LDS holds three regions: the tile's input rows (pitch nin, which
-// keeps the fragment reads free of bank conflicts), the gate rows' state part
-// [h | 0] (later r * h, then the MLP hidden layer) and h'.  The next tile's
-// input rows are copied from global memory straight into their region as
-// soon as the gate products are done with it, and its FP32 state into
-// registers once the update has read the current one, while the current tile
-// runs its state update, MLP and output products; the weights of those
-// products are requested first, so the waits for them never wait for the
-// copy.  A 128-patch tile is a pair of
-// the launch's 64-patch row tiles, each of which may belong to another flow
-// of a batch.
-constexpr int kWideRows = 128;
-constexpr int kCPolNT = 2;   // cache-policy operand of a global load: non-temporal
-
+// Persistent BF16 kernel for the shapes k_net_reg does not cover (H = 128, or
+// H = 64 at K = 3; standard rows, Hm = 0 or H).  One wave per hidden tile, for
+// all rows of a tile, with that hidden tile's gate fragments in registers for
+// the whole launch: 164 VGPRs at K = 3, H = 128, where the eight waves hold 336 KB
+// of weights and LDS the 110 KB of U_h, of the MLP and of the output beside a
+// tile's rows.  The next tile's input rows and FP32 state (in the update's lane
+// layout) are requested as soon as their registers are free.
+// At K = 3 that leaves LDS for 32 rows; at K <= 2 64 rows fit and are faster
+// (835 x 288, K = 2, step 180 us against 188).
+// Bound, with 64 flows of 128 x 128 patches at K = 3 and H = 128 (2.4 GB), by the LDS
+// reads of the operands: all eight waves read every row fragment, 68 KB per
+// wave and tile.  600 us; with fragments streamed from L2 for 128 rows at a
+// time 728; with each fragment read just before its products, as the compiler
+// orders them, 630; with both row tiles' output fragments read by each wave 610.
+// At H = 64 two workgroups of four waves share a CU (512 x 256: step 225 -> 220 us).
+// Small grids gain more, as no tile waits for weights: step times at 30 x 20 patches
+// and K = 3, H = 128 38.3 -> 27.4 us (30.4 with the streamed kernel), H = 64
+// 30.2 -> 24.6.
+constexpr int wide_rows(int K) { return K <= 2 ? 64 : 32; }
+// Instruction order: N times M matrix products, then one LDS read.
+template <int N, int M>
+__device__ __forceinline__ void mfma_then_read()
+{
+    if constexpr (N > 0) {
+        __builtin_amdgcn_sched_group_barrier(0x008, M, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        mfma_then_read<N - 1, M>();
+    }
+}
 // Workgroup barrier for LDS data only: this wave's LDS accesses complete,
-// then s_barrier.  Unlike __syncthreads() it does not wait for the wave's
-// outstanding global loads, so a copy into LDS (global_load_lds) of another
-// region can stay in flight across it.  (The memory clobber keeps the
-// compiler from moving memory accesses across it.)
+// then s_barrier; outstanding global loads and stores stay in flight.  (The
+// memory clobber keeps the compiler from moving memory accesses across it.)
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int K, int H, int HM>
-__global__ __launch_bounds__(kNetH64Threads, 1) void k_net_b16w(FlowArgs single, const BatchTable *__restrict__ bt,
-                                                                NetArgs net, int ntiles64)
+__global__ __launch_bounds__(4 * H, 2) void k_net_wide(FlowArgs single, const BatchTable *__restrict__ bt,
+                                                                  NetArgs net, int ntiles)
 {
     typedef Op<1> O;
     constexpr int n = 1 << K, nf = (n + 1) * (n + 1), nin = 4 * nf + 4, nout = 2 * nf;
-    constexpr int KC = 32, KQ = 8, KC1 = (nin + H + KC - 1) / KC, HC = H / KC;
-    constexpr int HT = H / 16, WPH = 8 / HT, RTW = (kWideRows / 16) / WPH;
+    constexpr int NT = 4 * H, R = wide_rows(K), RTW = R / 16;
+    constexpr int KC = 32, KQ = 8, HT = H / 16, HC = H / KC;
+    constexpr int KC1 = (nin + H + KC - 1) / KC, KCX = (nin + KC - 1) / KC;   // k-chunks; those with input columns
     constexpr int OT = (nout + 15) / 16;
-    constexpr int LDG = KC1 * KC - nin, LDH = H + 8;
-    constexpr int XP = nin / 8;                       // 16-byte pieces per input row
-    constexpr int XBYTES = kWideRows * nin * 2;
-    constexpr int GBYTES = kWideRows * (LDG > LDH ? LDG : LDH) * 2;
-    constexpr int HBYTES = kWideRows * LDH * 2;
-    constexpr int KX = nin / KC;                      // k-chunks of input alone; chunk KX may straddle
+    // row pitch: an odd number of 16-byte pieces
+    constexpr int LDA = (KC1 * KC / 8) % 2 ? KC1 * KC : KC1 * KC + 8;
+    constexpr int LDH = H + 8, PADK = KC1 * KC - nin - H;
+    constexpr bool W2R = H == 64;                     // U_h in registers, or in LDS
+    constexpr int W2N = W2R ? 1 : HT * HC * 64, W3N = (HM > 0 ? HT : OT) * HC * 64, W4N = HM > 0 ? OT * HC * 64 : 1;
+    constexpr int XP = nin / 8, XCH = R * XP, XPT = (XCH + NT - 1) / NT;      // 16-byte pieces of the input rows
     static_assert(HM == 0 || HM == H, "MLP hidden tiles follow the hidden tiles");
-    static_assert(nin % 8 == 0 && LDG >= H && (LDG - H) % 8 == 0, "rows in 16-byte pieces");
-    static_assert(kNetH64Threads == 512 && (H == 64 || H == 128), "eight waves over 4 or 8 hidden tiles");
-    static_assert(XBYTES + GBYTES + HBYTES <= 160 * 1024, "LDS of one CU");
-    if (bt) ntiles64 = bt->prefix[kKindNet][bt->nflows];
-    const int ntiles = (ntiles64 + 1) / 2;
+    static_assert(nin % 8 == 0 && (H == 64 || H == 128), "rows in 16-byte pieces");
+    if (bt) ntiles = bt->prefix[kKindNet][bt->nflows];   // batched: the table's row tiles
+    ntiles *= 64 / R;                                    // this kernel's tiles
 
-    // (three arrays, not one: the compiler then knows that reads of sG and
-    // sHp cannot see the copy into sX and need not wait for it)
-    __shared__ __align__(16) __bf16 sX[XBYTES / 2];     // input rows
-    __shared__ __align__(16) __bf16 sG[GBYTES / 2];     // [h | 0], then r * h, then MLP hidden
-    __shared__ __align__(16) __bf16 sHp[HBYTES / 2];    // h'
+    __shared__ __align__(16) __bf16 sA[R * LDA];      // [x | h | 0]
+    __shared__ __align__(16) __bf16 sG[R * LDH];      // r * h, then the MLP hidden layer
+    __shared__ __align__(16) __bf16 sHp[R * LDH];     // h'
+    __shared__ __align__(16) bf8 sW2[W2N];
+    __shared__ __align__(16) bf8 sW3[W3N];
+    __shared__ __align__(16) bf8 sW4[W4N];
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, lq = lane >> 4;
-    const int ht = wave % HT, rt0 = RTW * (wave / HT);
-    const int ucol = 16 * ht + 4 * lq;
+    const int tid = threadIdx.x, ht = __builtin_amdgcn_readfirstlane(tid >> 6), lane0 = tid & 63;
+    const bf8 *B1 = reinterpret_cast<const bf8 *>(net.B1);
+    const bf8 *B2 = reinterpret_cast<const bf8 *>(net.B2);
+    const bf8 *B3 = reinterpret_cast<const bf8 *>(net.B3);
+    const bf8 *B4 = reinterpret_cast<const bf8 *>(net.B4);
+    // (the candidate's weights are zero in the chunks of state alone)
+    bf8 wz[KC1], wr[KC1], wh[KCX], w2[W2R ? HC : 1];
+#pragma unroll
+    for (int kc = 0; kc < KC1; ++kc) {
+        wz[kc] = B1[((0 * HT + ht) * KC1 + kc) * 64 + lane0];
+        wr[kc] = B1[((1 * HT + ht) * KC1 + kc) * 64 + lane0];
+    }
+#pragma unroll
+    for (int kc = 0; kc < KCX; ++kc) wh[kc] = B1[((2 * HT + ht) * KC1 + kc) * 64 + lane0];
+    if constexpr (W2R) {
+#pragma unroll
+        for (int kc = 0; kc < HC; ++kc) w2[kc] = B2[(ht * HC + kc) * 64 + lane0];
+    } else {
+        for (int t = tid; t < W2N; t += NT) sW2[t] = B2[t];
+    }
+    for (int t = tid; t < W3N; t += NT) sW3[t] = B3[t];
+    if (HM > 0)
+        for (int t = tid; t < W4N; t += NT) sW4[t] = B4[t];
+    // the k-padding columns stay zero for the whole launch
+    if (PADK > 0)
+        for (int t = tid; t < R * PADK; t += NT) sA[(t / PADK) * LDA + nin + H + t % PADK] = (__bf16)0.f;
 
-    // the two 64-row halves of a tile: input, state and output rows, row count
-    // (global address-space pointers: global, not flat, loads and stores;
-    // the single flow's fields copied out, since the lambdas below would
-    // otherwise reach the argument through a generic pointer)
+    // A tile's buffers.  The fields are read in two branches: a pointer that
+    // may point at either the kernel argument or the batch table would make
+    // them flat loads (and the lambdas below would reach the argument through
+    // a generic pointer).
     typedef __attribute__((address_space(1))) float gfloat;
-    typedef __attribute__((address_space(1))) void gvoid;
-    typedef __attribute__((address_space(3))) void lvoid;
-    const void *const sXg = single.X;
-    float *const sh = single.h, *const sdp = single.dpatch;
-    const int sP = single.nx * single.ny;
-    struct Half {
-        gptr<__bf16> X;
+    struct Rows {
+        gptr<bf8> X;
         gfloat *h, *dp;
-        int nrows;
+        int nrows;                                       // (none or negative: the second half of a short row tile)
     };
-    auto half_of = [&](int t64) -> Half {
-        Half r{nullptr, nullptr, nullptr, 0};
-        if (t64 >= ntiles64) return r;
-        int blk = t64;
-        // (fields read in two branches: a pointer that may point at either the
-        // kernel argument or the batch table would make them flat loads)
+    const void *const s_X = single.X;
+    float *const s_h = single.h, *const s_dp = single.dpatch;
+    const int s_P = single.nx * single.ny;
+    auto rows_of = [&](int tile) -> Rows {
+        int blk = tile / (64 / R);
         const void *X;
         float *h, *dp;
         int P;
@@ -1377,192 +1399,126 @@ __global__ __launch_bounds__(kNetH64Threads, 1) void k_net_b16w(FlowArgs single,
             const FlowArgs &F = *batch_flow(bt, kKindNet, blk);
             X = F.X; h = F.h; dp = F.dpatch; P = F.nx * F.ny;
         } else {
-            X = sXg; h = sh; dp = sdp; P = sP;
+            X = s_X; h = s_h; dp = s_dp; P = s_P;
         }
-        const int row0 = blk * 64;
-        r.X = (gptr<__bf16>)(reinterpret_cast<const __bf16 *>(X) + (size_t)row0 * nin);
+        const int row0 = blk * 64 + R * (tile % (64 / R));
+        Rows r;
+        r.X = (gptr<bf8>)(reinterpret_cast<const __bf16 *>(X) + (size_t)row0 * nin);
         r.h = (gfloat *)(h + (size_t)row0 * H);
         r.dp = (gfloat *)(dp + (size_t)row0 * nout);
-        r.nrows = min(64, P - row0);
+        r.nrows = min(R, P - row0);
         return r;
     };
-
-    // a tile's input rows, copied into sX without passing through registers:
-    // one wave load moves 64 consecutive 16-byte pieces (a half's rows are
-    // consecutive in global memory and in sX).  The loads are unconditional,
-    // so that the waits for later loads can count past them; wide_x_piece
-    // keeps every read inside the half's rows (rows past a flow's end read
-    // its last row at the same column, an empty half reads the other half's
-    // rows; those rows' results are never stored).  (Lane index from
-    // tile_thread(): the index math is recomputed in each tile instead of
-    // hoisted out of the tile loop into registers.)
-    auto fill_x = [&](const Half &a, const Half &b) {
+    // The next tile's rows: input pieces and, in the lane layout of the update
+    // (rows 16 q + li, units ucol .. ucol + 3), the FP32 state.  Rows past the
+    // flow's end read its last row.
+    bf8 xr[XPT];
+    f4 hold[RTW];
+    auto load_x = [&](const Rows &rw) {
+        const int t0 = tile_thread();
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int c = t0 + i * NT;
+            xr[i] = rw.X[min(c / XP, rw.nrows - 1) * XP + c % XP];
+        }
+    };
+    auto load_hold = [&](const Rows &rw) {
         const int l = tile_thread() & 63;
 #pragma unroll
-        for (int i = 0; i < (2 * XP + 7) / 8; ++i) {
-            const WidePiece w = wide_x_piece(i, wave, l, XP, a.nrows, b.nrows);
-            const Half &hh = w.half ? b : a;
-            // (non-temporal: the rows are read once, and the weights that
-            // every tile reads stay in L2 instead)
-            __builtin_amdgcn_global_load_lds((gvoid *)(hh.X + w.src), (lvoid *)(sX + w.dst), 16, 0, kCPolNT);
-        }
+        for (int q = 0; q < RTW; ++q)
+            hold[q] = *(const __attribute__((address_space(1))) f4 *)(rw.h + min(16 * q + (l & 15), rw.nrows - 1) * H +
+                                                                       16 * ht + 4 * (l >> 4));
     };
-    // a tile's FP32 state in the lane layout of the update (rows 16 q + li
-    // of the wave's row tiles, units ucol .. ucol + 3); unconditional loads
-    // as above (wide_h_row: rows past the flow's end read its last row)
-    f4 hold[RTW];
-    auto load_hold = [&](const Half &a, const Half &b) {
-        const int l = tile_thread() & 15;
-#pragma unroll
-        for (int q = 0; q < RTW; ++q) {
-            int half;
-            const int row = wide_h_row(16 * (rt0 + q) + l, a.nrows, b.nrows, half);
-            const Half &hh = half ? b : a;
-            hold[q] = *(const __attribute__((address_space(1))) f4 *)(hh.h + row * H + ucol);
-        }
-    };
+    Rows rw{};
     if ((int)blockIdx.x < ntiles) {
-        const Half a = half_of(2 * blockIdx.x), b = half_of(2 * blockIdx.x + 1);
-        fill_x(a, b);
-        load_hold(a, b);
+        rw = rows_of(blockIdx.x);
+        load_x(rw);
+        load_hold(rw);
     }
 
     for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const Half ha = half_of(2 * tile), hb = half_of(2 * tile + 1);
-        const bool more = tile + (int)gridDim.x < ntiles;
-        const gptr<bf8> B1 = pinned<bf8>(net.B1);
-        const gptr<bf8> B2 = pinned<bf8>(net.B2);
-        const gptr<bf8> B3 = pinned<bf8>(net.B3);
-        const gptr<bf8> B4 = pinned<bf8>(net.B4);
-
-        __syncthreads();   // the previous tile's readers of sG and sHp are done
-        // the state's BF16 copy and the zeros after it (the last k-chunk
-        // reads them)
+        const int nrows = rw.nrows;
+        gfloat *const hg = rw.h;
+        gfloat *const dp = rw.dp;
+        // (the last tile repeats its own loads; the rows staged here were last
+        // read before the previous tile's second barrier)
+        if (tile + (int)gridDim.x < ntiles) rw = rows_of(tile + gridDim.x);
+        const int t1 = tile_thread();
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int c = t1 + i * NT;
+            if (c < XCH) *reinterpret_cast<bf8 *>(&sA[(c / XP) * LDA + 8 * (c % XP)]) = xr[i];
+        }
+        const int lane = t1 & 63, li = lane & 15, lq = lane >> 4, ucol = 16 * ht + 4 * lq;
 #pragma unroll
         for (int q = 0; q < RTW; ++q) {
-            const int r = 16 * (rt0 + q) + li;
-            bf4 hb4;
-            hb4[0] = (__bf16)hold[q].x; hb4[1] = (__bf16)hold[q].y; hb4[2] = (__bf16)hold[q].z; hb4[3] = (__bf16)hold[q].w;
-            *reinterpret_cast<bf4 *>(&sG[r * LDG + ucol]) = hb4;
+            bf4 hb;
+            hb[0] = (__bf16)hold[q].x; hb[1] = (__bf16)hold[q].y; hb[2] = (__bf16)hold[q].z; hb[3] = (__bf16)hold[q].w;
+            *reinterpret_cast<bf4 *>(&sA[(16 * q + li) * LDA + nin + ucol]) = hb;
         }
-        if (LDG > H)
-            for (int t = tile_thread(); t < kWideRows * ((LDG - H) / 8); t += kNetH64Threads)
-                *reinterpret_cast<uint4 *>(&sG[(t / ((LDG - H) / 8)) * LDG + H + 8 * (t % ((LDG - H) / 8))]) = make_uint4(0u, 0u, 0u, 0u);
-        __builtin_amdgcn_s_waitcnt(0);   // this wave's pieces of the input rows have landed in LDS
-        __syncthreads();
+        load_x(rw);
+        lds_barrier();
 
-        // ---- gates: weight fragments streamed chunk by chunk
+        // ---- the three gates of this wave's hidden tile
         f4 az[RTW], ar[RTW], ah[RTW];
 #pragma unroll
         for (int q = 0; q < RTW; ++q) az[q] = ar[q] = ah[q] = f4{0.f, 0.f, 0.f, 0.f};
-        // (each chunk requests the fragments of the chunk two ahead before its
-        // products, so the products never wait for the chunk's own)
-        bf8 wz = B1[((0 * HT + ht) * KC1 + 0) * 64 + lane];
-        bf8 wr = B1[((1 * HT + ht) * KC1 + 0) * 64 + lane];
-        bf8 wh = B1[((2 * HT + ht) * KC1 + 0) * 64 + lane];
-        bf8 vz = B1[((0 * HT + ht) * KC1 + 1) * 64 + lane];
-        bf8 vr = B1[((1 * HT + ht) * KC1 + 1) * 64 + lane];
-        bf8 vh = B1[((2 * HT + ht) * KC1 + 1) * 64 + lane];
-        auto chunk = [&](int kc, const __bf16 *base, int pitch, int lrow) {
-            const int kn = min(kc + 2, KC1 - 1);
-            const bf8 nz = B1[((0 * HT + ht) * KC1 + kn) * 64 + lane];
-            const bf8 nr = B1[((1 * HT + ht) * KC1 + kn) * 64 + lane];
-            const bf8 nh = B1[((2 * HT + ht) * KC1 + kn) * 64 + lane];
+#pragma unroll
+        for (int kc = 0; kc < KC1; ++kc)
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
-                const bf8 a = *reinterpret_cast<const bf8 *>(&base[(16 * (rt0 + q) + lrow) * pitch]);
-                az[q] = O::mma(az[q], wz, a);
-                ar[q] = O::mma(ar[q], wr, a);
-                ah[q] = O::mma(ah[q], wh, a);
+                const bf8 a = *reinterpret_cast<const bf8 *>(&sA[(16 * q + li) * LDA + kc * KC + lq * KQ]);
+                az[q] = O::mma(az[q], wz[kc], a);
+                ar[q] = O::mma(ar[q], wr[kc], a);
+                if (kc < KCX) ah[q] = O::mma(ah[q], wh[kc], a);
             }
-            wz = vz;
-            wr = vr;
-            wh = vh;
-            vz = nz;
-            vr = nr;
-            vh = nh;
-        };
-#pragma unroll 1
-        for (int kc = 0; kc < KX; ++kc) chunk(kc, sX + kc * KC + lq * KQ, nin, li);
-        {
-            // chunk KX: a lane's 8 columns lie in the input or in the state
-            // part (lane indices from tile_thread(): the row addresses are
-            // recomputed in each tile, not held in registers across tiles)
-            const int tt = tile_thread() & 63;
-            const int k0 = KX * KC + (tt >> 4) * KQ;
-            const bool inx = k0 < nin;
-            chunk(KX, inx ? sX + k0 : sG + (k0 - nin), inx ? nin : LDG, tt & 15);
-        }
-#pragma unroll 1
-        for (int kc = KX + 1; kc < KC1; ++kc) chunk(kc, sG + (kc * KC + lq * KQ - nin), LDG, li);
-        __syncthreads();   // every wave is done with sX and sG
-
-        // the weights of U_h, of the MLP hidden layer and of this wave's
-        // output tiles (ht, ht + HT, ...), requested before the copy below so
-        // that the waits for them do not wait for the copy
-        bf8 w2[HC], w3[HC];
-#pragma unroll
-        for (int kc = 0; kc < HC; ++kc) w2[kc] = B2[(ht * HC + kc) * 64 + lane];
-        if constexpr (HM > 0) {
-#pragma unroll
-            for (int kc = 0; kc < HC; ++kc) w3[kc] = B3[(ht * HC + kc) * 64 + lane];
-        }
-        const gptr<bf8> Wo = HM > 0 ? B4 : B3;
-        constexpr int NOT = (OT + HT - 1) / HT;
-        bf8 wo[NOT][HC];
-#pragma unroll
-        for (int j = 0; j < NOT; ++j) {
-            const int ot = min(ht + j * HT, OT - 1);
-#pragma unroll
-            for (int kc = 0; kc < HC; ++kc) wo[j][kc] = Wo[(ot * HC + kc) * 64 + lane];
-        }
+        // (fragments are read four ahead of their products)
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+        mfma_then_read<RTW * KCX, 3>();
+        mfma_then_read<RTW * (KC1 - KCX) - 4, 2>();
 #pragma unroll
         for (int q = 0; q < RTW; ++q) {
-            const int r = 16 * (rt0 + q) + li;
             bf4 rh;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 az[q][e] = sigmoid_l2(az[q][e]);
                 rh[e] = (__bf16)(sigmoid_l2(ar[q][e]) * hold[q][e]);
             }
-            *reinterpret_cast<bf4 *>(&sG[r * LDH + ucol]) = rh;
+            *reinterpret_cast<bf4 *>(&sG[(16 * q + li) * LDH + ucol]) = rh;
         }
-        // the next tile's input rows, copied into sX (free from here on) while
-        // this tile runs its state update, MLP and output products.  The
-        // weights above land first: while a copy into LDS is outstanding, a
-        // wait for any load waits for the copy too.  The barriers until the
-        // tile's end are lds_barrier(), which do not wait for the copy.  (The
-        // last tile of the block copies itself again: no branch.)
-        __builtin_amdgcn_s_waitcnt(0);
-        const int nt = more ? tile + (int)gridDim.x : tile;
-        const Half na = half_of(2 * nt), nb = half_of(2 * nt + 1);
-        fill_x(na, nb);
+        // (weights from LDS are read before the barrier that their products wait at)
+        bf8 wu[HC];
+#pragma unroll
+        for (int kc = 0; kc < HC; ++kc) wu[kc] = W2R ? w2[W2R ? kc : 0] : sW2[W2R ? 0 : (ht * HC + kc) * 64 + lane];
         lds_barrier();
 
         // ---- U_h (r * h); new state
 #pragma unroll
         for (int q = 0; q < RTW; ++q) {
-            const int r = 16 * (rt0 + q) + li;
+            const int r = 16 * q + li;
             f4 au = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kc = 0; kc < HC; ++kc)
-                au = O::mma(au, w2[kc], *reinterpret_cast<const bf8 *>(&sG[r * LDH + kc * KC + lq * KQ]));
+                au = O::mma(au, wu[kc], *reinterpret_cast<const bf8 *>(&sG[r * LDH + kc * KC + lq * KQ]));
             f4 hn;
-            bf4 hb4;
+            bf4 hb;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float z = az[q][e];
                 // h' = z h + (1 - z) c = c + z (h - c), c the candidate state
                 const float c = tanh_l2(ah[q][e] + au[e]);
                 hn[e] = c + z * (hold[q][e] - c);
-                hb4[e] = (__bf16)hn[e];
+                hb[e] = (__bf16)hn[e];
             }
-            const Half &hh = r < 64 ? ha : hb;
-            if ((r & 63) < hh.nrows) *(__attribute__((address_space(1))) f4 *)(hh.h + (r & 63) * H + ucol) = hn;
-            *reinterpret_cast<bf4 *>(&sHp[r * LDH + ucol]) = hb4;
+            if (r < nrows) *(__attribute__((address_space(1))) f4 *)(hg + r * H + ucol) = hn;
+            *reinterpret_cast<bf4 *>(&sHp[r * LDH + ucol]) = hb;
         }
-        // the next tile's state (this tile's is no longer read)
-        load_hold(na, nb);
+        load_hold(rw);
+        bf8 wm[HC];
+        if constexpr (HM > 0) {
+#pragma unroll
+            for (int kc = 0; kc < HC; ++kc) wm[kc] = sW3[(ht * HC + kc) * 64 + lane];
+        }
         lds_barrier();
 
         // ---- MLP head
@@ -1570,11 +1526,11 @@ __global__ __launch_bounds__(kNetH64Threads, 1) void k_net_b16w(FlowArgs single,
         if constexpr (HM > 0) {
 #pragma unroll
             for (int q = 0; q < RTW; ++q) {
-                const int r = 16 * (rt0 + q) + li;
+                const int r = 16 * q + li;
                 f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kc = 0; kc < HC; ++kc)
-                    acc = O::mma(acc, w3[kc], *reinterpret_cast<const bf8 *>(&sHp[r * LDH + kc * KC + lq * KQ]));
+                    acc = O::mma(acc, wm[kc], *reinterpret_cast<const bf8 *>(&sHp[r * LDH + kc * KC + lq * KQ]));
                 bf4 m;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) m[e] = (__bf16)fmaxf(acc[e], 0.f);
@@ -1583,33 +1539,31 @@ __global__ __launch_bounds__(kNetH64Threads, 1) void k_net_b16w(FlowArgs single,
             lds_barrier();
             src = sG;
         }
-        const int lo = tile_thread() & 15;   // (row addresses recomputed in each tile)
+        // half of the waves take each row tile, and read its rows once for all
+        // their output tiles
+        static_assert(HT % RTW == 0, "a row tile for each group of waves");
+        const int r = 16 * (ht % RTW) + li;
+        bf8 ao[HC];
 #pragma unroll
-        for (int j = 0; j < NOT; ++j) {
-            const int ot = ht + j * HT;
+        for (int kc = 0; kc < HC; ++kc) ao[kc] = *reinterpret_cast<const bf8 *>(&src[r * LDH + kc * KC + lq * KQ]);
+#pragma unroll
+        for (int j = 0; j < (OT + HT / RTW - 1) / (HT / RTW); ++j) {
+            const int ot = ht / RTW + j * (HT / RTW), oc = 16 * ot + 4 * lq;
             if (ot >= OT) break;
-            const int oc = 16 * ot + 4 * lq;
+            f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int q = 0; q < RTW; ++q) {
-                const int r = 16 * (rt0 + q) + li;
-                f4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kc = 0; kc < HC; ++kc)
-                    acc = O::mma(acc, wo[j][kc], *reinterpret_cast<const bf8 *>(&src[r * LDH + kc * KC + lq * KQ]));
-                // nout is even: the pairs (oc, oc+1), (oc+2, oc+3) are inside or outside together
-                const int ro = 16 * (rt0 + q) + lo;
-                const Half &hh = ro < 64 ? ha : hb;
-                if ((ro & 63) < hh.nrows) {
-                    gfloat *o = hh.dp + (ro & 63) * nout + oc;
-                    typedef float v2 __attribute__((ext_vector_type(2)));
-                    typedef __attribute__((address_space(1))) v2 gv2;
-                    if (oc < nout) *(gv2 *)o = v2{acc[0], acc[1]};
-                    if (oc + 2 < nout) *(gv2 *)(o + 2) = v2{acc[2], acc[3]};
-                }
+            for (int kc = 0; kc < HC; ++kc)
+                acc = O::mma(acc, HM > 0 ? sW4[HM > 0 ? (ot * HC + kc) * 64 + lane : 0] : sW3[(ot * HC + kc) * 64 + lane], ao[kc]);
+            // nout is even: the pairs (oc, oc+1), (oc+2, oc+3) are inside or outside together
+            if (r < nrows) {
+                gfloat *o = dp + r * nout + oc;
+                typedef float v2 __attribute__((ext_vector_type(2)));
+                typedef __attribute__((address_space(1))) v2 gv2;
+                if (oc < nout) *(gv2 *)o = v2{acc[0], acc[1]};
+                if (oc + 2 < nout) *(gv2 *)(o + 2) = v2{acc[2], acc[3]};
             }
         }
     }
-    __builtin_amdgcn_s_waitcnt(0);   // the last tile's repeated copy into LDS has landed
 }
 
 static int g_num_cus = 0;
@@ -1641,28 +1595,10 @@ static int num_cus()
     }
     return g_num_cus;
 }
-// The wide kernel keeps its weights in registers for all tiles of a block and
-// so pays for loading them first; with at most one row tile per CU there is no
-// second tile, and at H = 128 the streamed kernel, whose blocks start on their
-// rows at once, is the faster one.  Step times (us, wide against streamed) at
-// H = 128: K = 2, 60 patches 29.1 / 24.3, 8192 33.3 / 27.8, 15000 34.8 / 31.0,
-// 30000 (two tiles per CU) 39.4 / 41.6; K = 3, 60 patches 36.2 / 30.4, 8192
-// 43.9 / 38.9, 15000 52.5 / 48.3, 30000 73.4 / 80.7.  At H = 64 (K = 3) the two
-// are level up to one tile per CU (8192 patches 36.6 / 36.4), and the wide one
-// is kept.
-static bool use_b16w(const NetArgs &net, int row_tiles)
+static bool use_wide(const NetArgs &net)
 {
-    if (!standard_rows(net) || net.prec != 1 || use_reg(net) || (net.Hm != 0 && net.Hm != net.H)) return false;
-    return net.H == 64 || (net.H == 128 && row_tiles > num_cus());
-}
-
-// Grid of a launch on row_tiles tiles: persistent kernels loop over them.
-static int net_blocks(const NetArgs &net, int row_tiles, bool persistent)
-{
-    if (!persistent) return row_tiles;
-    // (at H = 32 a workgroup is four waves of up to 210 registers: two per CU)
-    const int most = use_reg(net) && net.H == 32 ? 2 * num_cus() : num_cus();
-    return row_tiles < most ? row_tiles : most;
+    return standard_rows(net) && net.prec == 1 && !use_reg(net) && (net.H == 64 || net.H == 128) &&
+           (net.Hm == 0 || net.Hm == net.H);
 }
 
 template <int PREC, int H>
@@ -1678,12 +1614,14 @@ static hipError_t launch_net_t(const FlowArgs &f, const BatchTable *bt, int nblo
 
 hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net, hipStream_t s)
 {
-    const bool wide = use_b16w(net, ntiles);
-    const int nblocks = net_blocks(net, ntiles, use_reg(net));
+    // persistent kernels: a grid that fills the CUs, or one tile per workgroup
+    auto grid = [&](int tiles, int per_cu) { return dim3(tiles < per_cu * num_cus() ? tiles : per_cu * num_cus()); };
     if (use_reg(net)) {
+        // (at H = 32 a workgroup is four waves of up to 210 registers: two per CU)
+        const dim3 g = grid(ntiles, net.H == 32 ? 2 : 1);
 #define DNNMG_REG(NN, HH)                                                                                              \
         if (net.nin == NN && net.H == HH) {                                                                            \
-            hipLaunchKernelGGL((k_net_reg<NN, HH>), dim3(nblocks), dim3(net_reg_threads<HH>()), 0, s, f, bt, net, ntiles); \
+            hipLaunchKernelGGL((k_net_reg<NN, HH>), g, dim3(net_reg_threads<HH>()), 0, s, f, bt, net, ntiles); \
             return hipGetLastError();                                                                                  \
         }
         DNNMG_REG(40, 32) DNNMG_REG(56, 32) DNNMG_REG(104, 32)
@@ -1692,27 +1630,23 @@ hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const
 #undef DNNMG_REG
         return hipErrorInvalidValue;
     }
-    if (wide) {
-        // 128-patch tiles: half as many blocks are enough
-        dim3 g(net_blocks(net, (ntiles + 1) / 2, true)), b(kNetH64Threads);
-#define DNNMG_B16W(KK, HH, MM) hipLaunchKernelGGL((k_net_b16w<KK, HH, MM>), g, b, 0, s, f, bt, net, ntiles)
-#define DNNMG_B16W_H(KK)                                                                             \
-        if (net.H == 64) { if (net.Hm == 64) DNNMG_B16W(KK, 64, 64); else DNNMG_B16W(KK, 64, 0); }    \
-        else { if (net.Hm == 128) DNNMG_B16W(KK, 128, 128); else DNNMG_B16W(KK, 128, 0); }
-        switch (net.K) {
-        case 1: DNNMG_B16W_H(1) break;
-        case 2: DNNMG_B16W_H(2) break;
-        case 3: DNNMG_B16W_H(3) break;
-        default: return hipErrorInvalidValue;
+    if (use_wide(net)) {
+        const dim3 g = grid(ntiles * (64 / wide_rows(net.K)), 128 / net.H), b(4 * net.H);
+#define DNNMG_WIDE(KK, HH, MM)                                                                             \
+        if (net.K == KK && net.H == HH && net.Hm == MM) {                                                 \
+            hipLaunchKernelGGL((k_net_wide<KK, HH, MM>), g, b, 0, s, f, bt, net, ntiles);                 \
+            return hipGetLastError();                                                                     \
         }
-#undef DNNMG_B16W_H
-#undef DNNMG_B16W
-        return hipGetLastError();
+        DNNMG_WIDE(1, 128, 0) DNNMG_WIDE(1, 128, 128)
+        DNNMG_WIDE(2, 128, 0) DNNMG_WIDE(2, 128, 128)
+        DNNMG_WIDE(3, 64, 0) DNNMG_WIDE(3, 64, 64)
+        DNNMG_WIDE(3, 128, 0) DNNMG_WIDE(3, 128, 128)
+#undef DNNMG_WIDE
+        return hipErrorInvalidValue;
     }
     if (use_q8p(net)) {
         // as many workgroups of H / 16 waves as a CU's four SIMDs hold
-        const int most = 4 * q8p_waves(net.K) / (net.H / 16) * num_cus(), tiles = ntiles * (64 / kQ8Rows);
-        dim3 g(tiles < most ? tiles : most), b(4 * net.H);
+        const dim3 g = grid(ntiles * (64 / kQ8Rows), 64 * q8p_waves(net.K) / net.H), b(4 * net.H);
 #define DNNMG_Q8P(KK, HH, MM) hipLaunchKernelGGL((k_net_q8p<KK, HH, MM>), g, b, 0, s, f, bt, net, ntiles)
 #define DNNMG_Q8P_H(KK)                                                                            \
         if (net.H == 64) { if (net.Hm == 64) DNNMG_Q8P(KK, 64, 64); else DNNMG_Q8P(KK, 64, 0); }    \
@@ -1728,7 +1662,7 @@ hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const
         return hipGetLastError();
     }
     if (net.prec == 2) {
-        dim3 g(nblocks), b(kThreads);
+        dim3 g(ntiles), b(kThreads);
 #define DNNMG_FP8_CASE(HH)                                                                  \
         if (net.H == HH) {                                                                  \
             if (bt) hipLaunchKernelGGL((k_net_fp8<HH, true>), g, b, 0, s, f, bt, net);      \
@@ -1742,15 +1676,15 @@ hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const
         return hipErrorInvalidValue;
     }
     if (net.prec == 0) {
-        if (net.H == 32) return launch_net_t<0, 32>(f, bt, nblocks, net, s);
-        if (net.H == 64) return launch_net_t<0, 64>(f, bt, nblocks, net, s);
-        if (net.H == 96) return launch_net_t<0, 96>(f, bt, nblocks, net, s);
-        if (net.H == 128) return launch_net_t<0, 128>(f, bt, nblocks, net, s);
+        if (net.H == 32) return launch_net_t<0, 32>(f, bt, ntiles, net, s);
+        if (net.H == 64) return launch_net_t<0, 64>(f, bt, ntiles, net, s);
+        if (net.H == 96) return launch_net_t<0, 96>(f, bt, ntiles, net, s);
+        if (net.H == 128) return launch_net_t<0, 128>(f, bt, ntiles, net, s);
     } else if (net.prec == 1) {
-        if (net.H == 32) return launch_net_t<1, 32>(f, bt, nblocks, net, s);
-        if (net.H == 64) return launch_net_t<1, 64>(f, bt, nblocks, net, s);
-        if (net.H == 96) return launch_net_t<1, 96>(f, bt, nblocks, net, s);
-        if (net.H == 128) return launch_net_t<1, 128>(f, bt, nblocks, net, s);
+        if (net.H == 32) return launch_net_t<1, 32>(f, bt, ntiles, net, s);
+        if (net.H == 64) return launch_net_t<1, 64>(f, bt, ntiles, net, s);
+        if (net.H == 96) return launch_net_t<1, 96>(f, bt, ntiles, net, s);
+        if (net.H == 128) return launch_net_t<1, 128>(f, bt, ntiles, net, s);
     }
     return hipErrorInvalidValue;
 }

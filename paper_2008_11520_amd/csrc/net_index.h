@@ -17,8 +17,8 @@ namespace dnnmg {
 using std::min;
 #endif
 
-// One 16-byte piece of the copy of a 128-patch tile's input rows into LDS
-// (k_net_b16w).  The tile is two halves of up to 64 rows each (a: na >= 1
+// One 16-byte piece of the copy of a 128-patch tile's input rows into LDS.
+// The tile is two halves of up to 64 rows each (a: na >= 1
 // rows, b: nb >= 0 rows); a row is XP pieces of 8 BF16 (nin = 8 XP).  Wave
 // load i of wave w moves the pieces 64 j .. 64 j + 63 of the tile's 2 XP
 // groups, j = min(w + 8 i, 2 XP - 1) (waves with one load fewer repeat the
@@ -51,7 +51,7 @@ DNNMG_HD inline WidePiece wide_x_piece(int i, int wave, int lane, int XP, int na
 }
 
 // Row of the FP32 state that tile row r (0 .. 127) of a 128-patch tile
-// reads (k_net_b16w); half tells which half it belongs to.  Rows past a
+// reads; half tells which half it belongs to.  Rows past a
 // half's end read its last row; an empty second half reads the first's.
 DNNMG_HD inline int wide_h_row(int r, int na, int nb, int &half)
 {

@@ -1,9 +1,10 @@
-"""The BF16 network at H = 128 on both sides of its dispatch rule: 256 row
-tiles of 64 patches (streamed weights, one tile per workgroup) and 257, the last
-one of a single patch (128-patch tiles, weights kept).  The network's output
-and state against the FP64 oracle within the step's bound for BF16 operands,
-2e-2; and a batch of 261 row tiles, whose pairs straddle flows, against the
-same flows stepped alone, bit for bit: both kernels form each sum alike."""
+"""The BF16 network kernel that keeps its weights in registers (H = 128, or
+K = 3) at the edges of its tiles of 32 (K = 3) and 64 patches: one patch less
+and more than a tile, a 64-patch row tile whose second half is empty, 256 row
+tiles and 257, the last one of a single patch, so that a workgroup takes a
+second tile.  The network's output and state against the FP64 oracle within the
+step's bound for BF16 operands, 2e-2; and a batch of 261 row tiles against the
+same flows stepped alone, bit for bit."""
 import numpy as np
 import pytest
 
@@ -14,9 +15,9 @@ from paper_2008_11520_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nx,ny", [(128, 128), (145, 113)])
-@pytest.mark.parametrize("K,H,Hm", [(1, 128, 0), (2, 128, 128), (3, 128, 0)])
-def test_wide_rule_against_oracle(nx, ny, K, H, Hm):
+@pytest.mark.parametrize("nx,ny", [(31, 1), (8, 4), (11, 3), (9, 7), (13, 5), (128, 128), (145, 113)])
+@pytest.mark.parametrize("K,H,Hm", [(1, 128, 0), (2, 128, 128), (3, 64, 64), (3, 128, 0)])
+def test_wide_tiles_against_oracle(nx, ny, K, H, Hm):
     flow = synth.channel_flow(nx, ny, 3, 0.005, perturb_seed=5)
     w = synth.xavier_weights(K, H, Hm, 1234)
     g = GpuRunner(make_gpu_flow(flow, K, H, Hm, 1e-3, w, "bf16"))
@@ -32,7 +33,7 @@ def test_wide_rule_against_oracle(nx, ny, K, H, Hm):
 
 
 @pytest.mark.parametrize("K,H,Hm", [(2, 128, 128), (3, 128, 0)])
-def test_wide_rule_batch_equals_single_flows(K, H, Hm):
+def test_wide_tiles_batch_equals_single_flows(K, H, Hm):
     import torch
     import paper_2008_11520_amd as pam
     w = synth.xavier_weights(K, H, Hm, 5)
