@@ -681,7 +681,13 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
     const float *dbar1 = reinterpret_cast<const float *>(s_dbar);
     const size_t P = (size_t)nx * ny;
     double *const pt = f.part + 2 * pt0;
-    for (int it = tid; it < TP * TP * 4; it += kThreads) {
+    //      At K = 3 a tile has 64 such items, one wave's, which the tile's other
+    //      waves waited out: four neighbouring lanes share one, lane `part` taking
+    //      the node rows part, part + 4 (and 8).  64 flows of 128 x 128 patches 527 ->
+    //      433 us (1.56 GB, which take 304), 30 x 20 patches, step 27.4 -> 26.2 us.
+    constexpr int PARTS = K == 3 ? 4 : 1;
+    for (int im = tid; im < TP * TP * 4 * PARTS; im += kThreads) {
+        const int part = im % PARTS, it = im / PARTS;
         const int cx = it & 1, comp = (it >> 1) & 1, pl = it >> 2;
         const int pi = pi0 + pl % TP, pj = pj0 + pl / TP;
         if (pi >= nx || pj >= ny) continue;
@@ -698,8 +704,9 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         const int rot = (pl / TP) % RR;
         double S[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
 #pragma unroll
-        for (int b0 = 0; b0 <= n; ++b0) {
-            const int b = b0 + rot > n ? b0 + rot - (n + 1) : b0 + rot;
+        for (int b0 = 0; b0 <= n; b0 += PARTS) {
+            const int b = PARTS > 1 ? b0 + part : (b0 + rot > n ? b0 + rot - (n + 1) : b0 + rot);
+            if (PARTS > 1 && b > n) break;
             double s0 = 0.0, s1 = 0.0;
 #pragma unroll
             for (int a = 0; a <= n; ++a) {
@@ -719,11 +726,18 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         double *const pq = pt + 2 * (size_t)cx * P + 2 * ((pl / TP) * nx + pl % TP) + comp;
         const int cb = (pl / TP) * SV + (pl % TP);
         const float *v1 = reinterpret_cast<const float *>(s_v);
+        double sum[2];
 #pragma unroll
         for (int cy = 0; cy < 2; ++cy) {
             const double S0 = S[cy][0], S1 = S[cy][1], S2 = S[cy][2];
+            sum[cy] = d0 * S0 + d1 * S1 + d2 * S2;
+            if constexpr (PARTS > 1) {
+                sum[cy] += lane_xor<1>(sum[cy]);
+                sum[cy] += lane_xor<2>(sum[cy]);
+            }
+        }
+        auto store = [&](int cy, double acc) {
             const int c = cx + 2 * cy;
-            double acc = d0 * S0 + d1 * S1 + d2 * S2;
             if constexpr (!UB) {
                 const double vq[4] = {(double)v1[2 * cb + comp], (double)v1[2 * (cb + 1) + comp],
                                       (double)v1[2 * (cb + SV) + comp], (double)v1[2 * (cb + SV + 1) + comp]};
@@ -737,6 +751,12 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
             double b = f.inv_dt64 * acc;
             if constexpr (CN) b -= th_old * s_T[8 * pl + 2 * c + comp];
             pq[4 * cy * P] = b;
+        };
+        if constexpr (PARTS > 1) {
+            if (part < 2) store(part, part ? sum[1] : sum[0]);
+        } else {
+            store(0, sum[0]);
+            store(1, sum[1]);
         }
     }
 }
@@ -744,9 +764,9 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
 // Single flow: one tile per block.  Batched: the blocks stride over the
 // table's tiles of all flows, so the grid need not match the batch.
 // Waves per SIMD the rhs aims at (what its LDS allows; register budget 512 /
-// waves; K = 3 needs more registers than 5 waves leave).
+// waves).
 template <int K>
-constexpr int rhs_waves() { return K == 2 ? 6 : (K == 3 ? 5 : 4); }
+constexpr int rhs_waves() { return K == 1 ? 4 : 6; }
 
 // The theta scheme (Crank-Nicolson), single flow.
 template <int K, int FROM_PATCHES>
