@@ -330,7 +330,7 @@ struct dnnmg_batch {
     RhsTables tab{};
     int cap = 0;                                // grid of every batched launch in a graph
     // grid of the one-tile-per-block launches (the one-launch tiles and the
-    // rhs after them) in the captured graph: at least their tiles, grown
+    // rhs after them; at K = 3 the defect and the rhs) in the captured graph: at least their tiles, grown
     // (and the graph captured again) when a membership has more
     int tile_grid = 0;
     // captured launch sequence.  Every per-flow argument and the tile counts
@@ -1607,12 +1607,13 @@ static int batch_enqueue(dnnmg_batch *b, bool graph, hipStream_t st)
     FlowArgs dummy{};
     int grid[kKinds];
     for (int k = 0; k < kKinds; ++k) grid[k] = graph ? b->cap : std::min(b->totals[k], b->cap);
-    // the one-launch tiles and the rhs of the tile frame take one tile per block
+    // the one-launch tiles, the rhs of the tile frame and at K = 3 the defect and
+    // the rhs take one tile per block
     auto tiles = [&](int k) { return graph ? b->tile_grid : b->totals[k]; };
     if (fused_step(b->net)) {
         HIP_OR_FAIL(launch_defect_net(dummy, b->dev, tiles(kKindDefect), b->net, st));
     } else {
-        HIP_OR_FAIL(launch_defect(dummy, b->dev, grid[kKindDefect], b->K, b->xfmt, st));
+        HIP_OR_FAIL(launch_defect(dummy, b->dev, b->K == 3 ? tiles(kKindDefect) : grid[kKindDefect], b->K, b->xfmt, st));
         HIP_OR_FAIL(launch_net(dummy, b->dev, grid[kKindNet], b->net, st));
     }
     if (b->frame) HIP_OR_FAIL(launch_rhs(dummy, b->dev, tiles(kKindRhs), b->K, b->tab, 2, st));
@@ -1628,9 +1629,8 @@ extern "C" int dnnmg_batch_launch(dnnmg_batch *b, int use_graph, void *stream)
     hipStream_t st = (hipStream_t)stream;
     if (!use_graph) return batch_enqueue(b, false, st);
     if (!st) return fail(DNNMG_EINVAL, "graph launches need a non-default stream");
-    // (only the one-launch batches have one-tile-per-block launches)
-    const int tiles = fused_step(b->net) ? std::max(b->totals[kKindDefect], b->totals[kKindRhs])
-                                         : (b->K == 3 ? b->totals[kKindRhs] : 0);
+    // (only the one-launch batches and K = 3 have one-tile-per-block launches)
+    const int tiles = fused_step(b->net) || b->K == 3 ? std::max(b->totals[kKindDefect], b->totals[kKindRhs]) : 0;
     const bool same = b->exec && b->graph_K == b->K && b->graph_xfmt == b->xfmt &&
                       b->graph_gather == b->gather && b->graph_frame == b->frame && tiles <= b->tile_grid &&
                       same_net(b->graph_net, b->net) &&

@@ -1109,42 +1109,56 @@ __device__ __forceinline__ void defect_tile(const FlowArgs &f, int blk, const Ne
 }
 
 // Single flow: one tile per block.  Batched: the blocks stride over the
-// table's tiles of all flows, so the grid need not match the batch.
+// table's tiles of all flows, so the grid need not match the batch; at K = 3
+// one tile per block, with the single-flow code: the loop over tiles costs
+// 7 VGPRs, and 2048 blocks of the same number of tiles do not come out even
+// at 5 blocks per CU (64 flows of 128 x 128: 717 us with 4 waves per SIMD, 679 with 5,
+// one tile per block 585; the vector instructions alone take 448).
 // Waves per SIMD the defect aims at (register budget 512 / waves): 4, or
-// what its LDS allows (K = 1 tiles hold more patches; FP32 input rows).
+// what its LDS allows (K = 1 tiles hold more patches; FP32 input rows); 5 at
+// K = 3, for one spilled value (512 x 256: step 237 -> 231 us).
 template <int K, typename XT>
 constexpr int defect_waves()
 {
-    return K == 1 ? (std::is_same<XT, float>::value ? 2 : 3) : (K == 2 && std::is_same<XT, float>::value ? 3 : 4);
+    return K == 1 ? (std::is_same<XT, float>::value ? 2 : 3) : (K == 2 ? (std::is_same<XT, float>::value ? 3 : 4) : (sizeof(XT) == 4 ? 4 : 5));
 }
 
 template <int K, typename XT, bool BATCHED>
 __global__ __launch_bounds__(kThreads, (defect_waves<K, XT>())) void k_defect(FlowArgs single, const BatchTable *__restrict__ bt)
 {
-    if (!BATCHED) {
+    if constexpr (!BATCHED) {
         defect_tile<K, XT, false>(single, xcd_tile(blockIdx.x, gridDim.x));
-        return;
-    }
-    const int total = bt->prefix[kKindDefect][bt->nflows];
-#pragma unroll 1
-    for (int g = blockIdx.x; g < total; g += gridDim.x) {
-        int blk = xcd_tile(g, total);
+    } else if constexpr (K == 3) {
+        // one tile per block, with the single-flow tile code
+        const int total = bt->prefix[kKindDefect][bt->nflows];
+        if ((int)blockIdx.x >= total) return;
+        int blk = xcd_tile(blockIdx.x, total);
         const FlowArgs &f = *batch_flow(bt, kKindDefect, blk);
-        defect_tile<K, XT, true>(f, blk);
-        __syncthreads();   // LDS is reused by the next tile
+        defect_tile<K, XT, false>(f, blk);
+    } else {
+        const int total = bt->prefix[kKindDefect][bt->nflows];
+#pragma unroll 1
+        for (int g = blockIdx.x; g < total; g += gridDim.x) {
+            int blk = xcd_tile(g, total);
+            const FlowArgs &f = *batch_flow(bt, kKindDefect, blk);
+            defect_tile<K, XT, true>(f, blk);
+            __syncthreads();   // LDS is reused by the next tile
+        }
     }
 }
 
 // The theta scheme (Crank-Nicolson) and/or the paper's network input, single flow.
 // (at K = 1 the paper's wider input rows leave LDS for one workgroup fewer)
-template <int K, typename XT, bool PAPER>
+// (the theta scheme needs 114 to 117 registers; with 96 and 31 spilled 73 us
+// for 63 at 1024 x 256 and K = 2)
+template <int K, typename XT, bool CN, bool PAPER>
 constexpr int defect_form_waves()
 {
-    return PAPER && K == 1 ? defect_waves<K, XT>() - 1 : defect_waves<K, XT>();
+    return PAPER && K == 1 ? defect_waves<K, XT>() - 1 : (CN && K == 3 ? 4 : defect_waves<K, XT>());
 }
 
 template <int K, typename XT, bool CN, bool PAPER>
-__global__ __launch_bounds__(kThreads, (defect_form_waves<K, XT, PAPER>())) void k_defect_form(FlowArgs single)
+__global__ __launch_bounds__(kThreads, (defect_form_waves<K, XT, CN, PAPER>())) void k_defect_form(FlowArgs single)
 {
     defect_tile<K, XT, false, false, 0, CN, PAPER>(single, xcd_tile(blockIdx.x, gridDim.x));
 }
