@@ -92,11 +92,14 @@ template <> struct Op<1> {
 
 
 // Streamed kernel: FP32 operands, and the BF16 shapes that the persistent
-// kernels below do not cover (H = 32, 96; the paper's network; the reset after
-// U_h; an MLP width other than 0 or H).
+// kernels below do not cover (H = 32 or 96 at K = 3; the reset after U_h at H = 128
+// or K = 3; an MLP width other than 0 or H) or are slower for (H >= 96 on few
+// patches, see launch_net).
 //
-// A workgroup takes 64 patches.  Wave w owns hidden tile w % HT for RT of the
-// four row tiles, so the workgroup reads each weight fragment once from L2 (twice
+// A workgroup takes R = 64 patches (16 where there are few: the products of one
+// row tile follow each other on one matrix core, so a grid that does not fill
+// the chip is timed by them).  Wave w owns hidden tile w % HT for RT of the
+// row tiles, so the workgroup reads each weight fragment once from L2 (twice
 // at H = 32) and every fragment feeds RT row tiles.  The operand rows
 // [x | h | 0] lie in LDS at a pitch of an odd number of 16-byte pieces (the 16
 // rows of a fragment read fall in distinct banks); once the gate products are
@@ -116,7 +119,7 @@ template <> struct Op<1> {
 struct StreamRows {
     int lda, bytes;   // row pitch in elements, and LDS bytes of the tile
 };
-template <int PREC, int H>
+template <int PREC, int H, int R>
 __host__ __device__ inline StreamRows stream_rows(int kc1, int Hm)
 {
     typedef Op<PREC> O;
@@ -126,25 +129,28 @@ __host__ __device__ inline StreamRows stream_rows(int kc1, int Hm)
     r.lda = (w / V) % 2 ? w : w + V;
     const int ldh = H + V, ldm = Hm > 0 ? Hm + V : 0;
     const int tail = ldh + (ldh > ldm ? ldh : ldm);      // h', then r * h and the MLP hidden layer
-    r.bytes = kNetRows * (r.lda > tail ? r.lda : tail) * (int)sizeof(typename O::T);
+    r.bytes = R * (r.lda > tail ? r.lda : tail) * (int)sizeof(typename O::T);
     return r;
 }
 
 // Waves of a workgroup: one per hidden tile, at least four; at H = 96 two per
 // hidden tile (six waves would load the four SIMDs unevenly: 300 x 200 patches,
 // K = 2, FP32 step 159.8 -> 140.1 us), and registers for two workgroups per CU.
-template <int H> constexpr int stream_waves() { return H == 96 ? 12 : (H / 16 < 4 ? 4 : H / 16); }
-template <int H> constexpr int stream_simd_waves() { return H == 96 ? 6 : 2; }
+constexpr int kFewRows = 16;   // patches of a workgroup where there are few (see launch_net_t)
+template <int H, int R> constexpr int stream_waves() { return R < 64 ? H / 16 * (R / 16) : (H == 96 ? 12 : (H / 16 < 4 ? 4 : H / 16)); }
+template <int H, int R> constexpr int stream_simd_waves() { return H == 96 && R == 64 ? 6 : 2; }
 
-template <int PREC, int H>
+template <int PREC, int H, int R>
 __device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const NetArgs &net, unsigned char *lds)
 {
     typedef Op<PREC> O;
     typedef typename O::T T;
     typedef typename O::Frag Frag;
     constexpr int KC = O::KC, KQ = O::KQ, HC = H / KC, V = 16 / (int)sizeof(T);
-    constexpr int HT = H / 16, NW = stream_waves<H>(), NT = 64 * NW, RT = 4 * HT / NW;
-    constexpr int AHEAD = PREC == 0 ? 1 : 2;     // k-chunks requested ahead: a chunk's products take 4 times as long in FP32
+    constexpr int HT = H / 16, NW = stream_waves<H, R>(), NT = 64 * NW, RT = R / 16 * HT / NW;
+    // k-chunks requested ahead: a chunk's products take 4 times as long in FP32,
+    // and one row tile's a quarter of four's
+    constexpr int AHEAD = R < 64 ? 4 : (PREC == 0 ? 1 : 2);
     constexpr int LDH = H + V;
     typedef T T4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(1))) float gfloat;
@@ -155,16 +161,16 @@ __device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const Ne
     const int P = f.nx * f.ny;
     const int nin = net.nin, nout = net.nout, Hm = net.Hm, kc1 = net.kc1;
     const bool reset_after = net.reset_after != 0;
-    const int lda = stream_rows<PREC, H>(kc1, Hm).lda, ldm = Hm + V;
+    const int lda = stream_rows<PREC, H, R>(kc1, Hm).lda, ldm = Hm + V;
     const int tid = tile_thread();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int li = lane & 15, lq = lane >> 4;
     const int ht = wave % HT, rt0 = RT * (wave / HT);
     const int ucol = 16 * ht + 4 * lq;
-    const int row0 = blk * kNetRows, nrows = min(kNetRows, P - row0);
+    const int row0 = blk * R, nrows = min(R, P - row0);
 
     T *const sA = reinterpret_cast<T *>(lds);          // [x | h | 0]
-    T *const sHp = sA, *const sR = sA + kNetRows * LDH, *const sAm = sR;
+    T *const sHp = sA, *const sR = sA + R * LDH, *const sAm = sR;
     const gptr<Frag> B1 = pinned<Frag>(net.B1);
     const gptr<Frag> B2 = pinned<Frag>(net.B2);
     const gptr<Frag> B3 = pinned<Frag>(net.B3);
@@ -180,7 +186,7 @@ __device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const Ne
         typedef unsigned int u4 __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(1))) const u4 gu4;
         gu4 *const X = (gu4 *)(reinterpret_cast<const T *>(f.X) + (size_t)row0 * nin);
-        const unsigned pr = (unsigned)nin / V, np = kNetRows * pr, in = (unsigned)nrows * pr;   // pieces per row, per tile, inside
+        const unsigned pr = (unsigned)nin / V, np = R * pr, in = (unsigned)nrows * pr;   // pieces per row, per tile, inside
         const unsigned inv = ((1u << 24) + pr - 1) / pr;      // c / pr = c inv >> 24 (c < 64 pr, pr < 128: exact)
         constexpr int U = PREC == 0 ? 7 : 4;
         for (unsigned c0 = tid; c0 < np; c0 += U * NT) {
@@ -219,7 +225,7 @@ __device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const Ne
         *reinterpret_cast<T4 *>(&sA[r * lda + nin + ucol]) = hb;
     }
     for (int z = nin + H + 4 * (tid & 3); z < kc1 * KC; z += 16)       // the k-padding
-        for (int r = tid >> 2; r < kNetRows; r += NT / 4) *reinterpret_cast<T4 *>(&sA[r * lda + z]) = T4{};
+        for (int r = tid >> 2; r < R; r += NT / 4) *reinterpret_cast<T4 *>(&sA[r * lda + z]) = T4{};
     __syncthreads();
 
     // ---- phase 1: [x | h] against [W_g | U_g], g = z, r, h (U_h comes in phase 2)
@@ -342,12 +348,12 @@ __device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const Ne
 
 // Single flow: one tile per block.  Batched: the blocks stride over the
 // table's tiles of all flows, so the grid need not match the batch.
-template <int PREC, int H, bool BATCHED>
-__global__ __launch_bounds__(64 * stream_waves<H>(), stream_simd_waves<H>()) void k_net(FlowArgs single, const BatchTable *__restrict__ bt, NetArgs net)
+template <int PREC, int H, int R, bool BATCHED>
+__global__ __launch_bounds__(64 * (stream_waves<H, R>()), (stream_simd_waves<H, R>())) void k_net(FlowArgs single, const BatchTable *__restrict__ bt, NetArgs net)
 {
     extern __shared__ __align__(16) unsigned char s_rows[];
     if (!BATCHED) {
-        stream_tile<PREC, H>(single, blockIdx.x, net, s_rows);
+        stream_tile<PREC, H, R>(single, blockIdx.x, net, s_rows);
         return;
     }
     const int total = bt->prefix[kKindNet][bt->nflows];
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(64 * stream_waves<H>(), stream_simd_waves<H>()) voi
     for (int g = blockIdx.x; g < total; g += gridDim.x) {
         int blk = g;
         const FlowArgs &f = *batch_flow(bt, kKindNet, blk);
-        stream_tile<PREC, H>(f, blk, net, s_rows);
+        stream_tile<PREC, H, R>(f, blk, net, s_rows);
         __syncthreads();   // LDS is reused by the next tile
     }
 }
@@ -1601,22 +1607,42 @@ static bool use_wide(const NetArgs &net)
            (net.Hm == 0 || net.Hm == net.H);
 }
 
+template <int PREC, int H, int R, bool BATCHED>
+static hipError_t launch_net_r(const FlowArgs &f, const BatchTable *bt, int nblocks, const NetArgs &net, hipStream_t s)
+{
+    const int lds = stream_rows<PREC, H, R>(net.kc1, net.Hm).bytes;
+    hipLaunchKernelGGL((k_net<PREC, H, R, BATCHED>), dim3(nblocks), dim3(64 * stream_waves<H, R>()), lds, s, f, bt, net);
+    return hipGetLastError();
+}
+
 template <int PREC, int H>
-static hipError_t launch_net_t(const FlowArgs &f, const BatchTable *bt, int nblocks, const NetArgs &net,
+static hipError_t launch_net_t(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net,
                                hipStream_t s)
 {
-    const int lds = stream_rows<PREC, H>(net.kc1, net.Hm).bytes;
-    const dim3 g(nblocks), b(64 * stream_waves<H>());
-    if (bt) hipLaunchKernelGGL((k_net<PREC, H, true>), g, b, lds, s, f, bt, net);
-    else hipLaunchKernelGGL((k_net<PREC, H, false>), g, b, lds, s, f, bt, net);
-    return hipGetLastError();
+    if (bt) return launch_net_r<PREC, H, 64, true>(f, bt, ntiles, net, s);
+    // few patches: 16 a workgroup, up to two workgroups per CU.  Step times (us, 64
+    // against 16) in FP32: K = 2, H = 64 2400 patches 33.1 / 25.4, 8192 35.2 / 30.8, 16384
+    // 37.4 / 39.7; K = 1, H = 32 256 patches 23.4 / 22.0, 8192 25.1 / 24.9; K = 3, H = 128
+    // 60 patches 76.3 / 39.8, 8192 86.4 / 67.0, 16384 97.8 / 113.0.  BF16 with an MLP of 256:
+    // 600 patches 24.4 / 22.3, 8192 26.4 / 25.3, 20000 33.2 / 36.1.
+    const int P = f.nx * f.ny;
+    if (P <= 2 * kFewRows * num_cus()) return launch_net_r<PREC, H, kFewRows, false>(f, bt, (P + kFewRows - 1) / kFewRows, net, s);
+    return launch_net_r<PREC, H, 64, false>(f, bt, ntiles, net, s);
 }
 
 hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net, hipStream_t s)
 {
     // persistent kernels: a grid that fills the CUs, or one tile per workgroup
     auto grid = [&](int tiles, int per_cu) { return dim3(tiles < per_cu * num_cus() ? tiles : per_cu * num_cus()); };
-    if (use_reg(net)) {
+    // With at most 16 patches per CU a workgroup of the persistent kernels has
+    // one tile for the weights it loads; from H = 96 on the streamed kernel's
+    // 16-patch tiles are then faster (step us, persistent against streamed): K = 2,
+    // H = 96 400 patches 23.9 / 22.3, 2400 24.7 / 22.5, 6000 25.5 / 25.3, 12288 27.6 / 30.6;
+    // K = 2, H = 128 2400 26.0 / 23.0; K = 3, H = 128 2400 27.7 / 26.6, 6000 33.7 / 35.0.  At H = 32
+    // and 64 they are level (K = 2, H = 64 400 patches 22.3 / 22.5, 2400 22.9 / 22.0; K = 3,
+    // H = 64 24.7 / 25.2).
+    const bool few = !bt && net.H >= 96 && f.nx * f.ny <= kFewRows * num_cus();
+    if (!few && use_reg(net)) {
         // (at H = 32 a workgroup is four waves of up to 210 registers: two per CU)
         const dim3 g = grid(ntiles, net.H == 32 ? 2 : 1);
 #define DNNMG_REG(NN, HH)                                                                                              \
@@ -1630,7 +1656,7 @@ hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const
 #undef DNNMG_REG
         return hipErrorInvalidValue;
     }
-    if (use_wide(net)) {
+    if (!few && use_wide(net)) {
         const dim3 g = grid(ntiles * (64 / wide_rows(net.K)), 128 / net.H), b(4 * net.H);
 #define DNNMG_WIDE(KK, HH, MM)                                                                             \
         if (net.K == KK && net.H == HH && net.Hm == MM) {                                                 \
