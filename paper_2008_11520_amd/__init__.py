@@ -136,9 +136,13 @@ def workspace_bytes(cfg: Config) -> int:
 
 
 def _stream(stream):
+    """The stream's handle; None: torch's current stream.  Small steps are as
+    fast as the host enqueues them: torch.cuda.current_stream() builds a Stream
+    object on each call (3.0 us, twice a step; the handle alone 0.4 us; 32 x 8
+    patches, K = 2, 18.8 -> 17.3 us a step)."""
     import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
