@@ -1191,13 +1191,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_defect_net(FlowArgs single, con
 constexpr int kSmallThreads = 512;
 static bool defect_small(int ntiles, int per_cu)
 {
-    // (a constant of the machine, read once)
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        (void)hipGetDevice(&dev);
-        return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 256;
-    }();
-    return ntiles <= per_cu * cus;
+    return ntiles <= per_cu * num_cus();
 }
 
 template <int HM>

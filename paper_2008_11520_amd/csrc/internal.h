@@ -199,6 +199,8 @@ hipError_t launch_defect(const FlowArgs &f, const BatchTable *bt, int nblocks, i
 // the network input never leaves LDS.  fused_step tells whether it applies.
 bool fused_step(const NetArgs &net);
 hipError_t launch_defect_net(const FlowArgs &f, const BatchTable *bt, int nblocks, const NetArgs &net, hipStream_t s);
+// Compute units of the device.
+int num_cus();
 // FP8 activation quantiser (stage entry point): rows x cols FP32 -> codes, scales.
 hipError_t launch_quantize(const float *a, int rows, int cols, uint8_t *q, float *s, hipStream_t st);
 hipError_t launch_net(const FlowArgs &f, const BatchTable *bt, int ntiles, const NetArgs &net,

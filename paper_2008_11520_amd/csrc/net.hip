@@ -1572,8 +1572,6 @@ __global__ __launch_bounds__(4 * H, 2) void k_net_wide(FlowArgs single, const Ba
     }
 }
 
-static int g_num_cus = 0;
-
 // The persistent kernels take rows of the standard width 4 nf + 4 and the
 // GRU as printed; other forms run the generic kernels.
 static bool standard_rows(const NetArgs &net)
@@ -1591,15 +1589,15 @@ static bool use_q8p(const NetArgs &net)
 {
     return standard_rows(net) && net.prec == 2 && (net.H == 64 || net.H == 128) && (net.Hm == 0 || net.Hm == net.H);
 }
-static int num_cus()
+int num_cus()
 {
-    if (g_num_cus == 0) {
-        int dev = 0;
+    // (a constant of the machine, read once)
+    static const int cus = [] {
+        int dev = 0, n = 0;
         (void)hipGetDevice(&dev);
-        if (hipDeviceGetAttribute(&g_num_cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            g_num_cus = 256;
-    }
-    return g_num_cus;
+        return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 256;
+    }();
+    return cus;
 }
 static bool use_wide(const NetArgs &net)
 {

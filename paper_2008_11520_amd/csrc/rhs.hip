@@ -27,6 +27,8 @@
 
 namespace dnnmg {
 
+constexpr int kRhsFew = 16;       // averaging / rhs tile on small grids
+
 template <int K>
 __device__ inline bool dirichlet_node(unsigned dir, int I, int J, int NX, int NY)
 {
@@ -81,10 +83,10 @@ __device__ __forceinline__ double lane_xor(double x)
 // neighbouring lanes and are summed with a fixed butterfly.  map: the first
 // item's map vectors (load_map64, clamped into the mesh), requested with the
 // tile's other loads.
-template <int K>
+template <int K, int TF>
 __device__ __forceinline__ void load_map64(const FlowArgs &f, int it, int pi0, int pj0, double2 (&m)[3])
 {
-    constexpr int n = 1 << K, TP = kRhsFine / n;
+    constexpr int n = 1 << K, TP = TF / n;
     const int pl = min(it / n, TP * TP - 1);
     const int pi = min(pi0 + pl % TP, f.nx - 1), pj = min(pj0 + pl / TP, f.ny - 1);
     const double2 *src = reinterpret_cast<const double2 *>(f.map64) + 4 * ((size_t)pj * f.nx + pi);
@@ -92,12 +94,12 @@ __device__ __forceinline__ void load_map64(const FlowArgs &f, int it, int pi0, i
     for (int k = 0; k < 3; ++k) m[k] = src[k];
 }
 
-template <int K>
+template <int K, int TF>
 __device__ __forceinline__ void transport_corners(const FlowArgs &f, int tid, int pi0, int pj0, const float2 *s_v,
                                                   const float2 *s_dbar, double *s_T, const double2 (&map)[3])
 {
     constexpr int n = 1 << K;
-    constexpr int TP = kRhsFine / n, NO = kRhsFine + 1;
+    constexpr int TP = TF / n, NO = TF + 1;
     constexpr int NI = TP * TP * n;
     static_assert(kThreads % n == 0, "a patch's rows on neighbouring lanes of one wave");
     constexpr double inv_n = 1.0 / n, wq = 0.25 / n;   // (the weight, times n)
@@ -111,7 +113,7 @@ __device__ __forceinline__ void transport_corners(const FlowArgs &f, int tid, in
         double acc[4][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
         if (it < NI && pi0 + pa < nx && pj0 + pb < ny) {
             double2 m[3] = {map[0], map[1], map[2]};
-            if (it0 > 0) load_map64<K>(f, it, pi0, pj0, m);
+            if (it0 > 0) load_map64<K, TF>(f, it, pi0, pj0, m);
             const double exx = m[0].x, exy = m[0].y, eyx = m[1].x, eyy = m[1].y, twx = m[2].x, twy = m[2].y;
             constexpr int SV = TP + 2;     // the rhs tile's corner layout
             const int c = pb * SV + pa;
@@ -224,7 +226,7 @@ __device__ __forceinline__ void transport_corners(const FlowArgs &f, int tid, in
     }
 }
 
-// One workgroup per tile of kRhsFine x kRhsFine fine elements (TP x TP patches).
+// One workgroup per tile of TF x TF fine elements (TP x TP patches).
 // FROM_PATCHES = 1: average f.dpatch and store the corrected velocity (the
 // step); 2: the same step after the one-launch K = 2 kernel, which has
 // averaged every node inside the tile's boundary lines already (frame.h):
@@ -236,7 +238,7 @@ __device__ __forceinline__ void transport_corners(const FlowArgs &f, int tid, in
 // against the hat moments: P v is bilinear on the patch, so its fine
 // interpolant is itself, and R (1/dt) M u needs no separate coarse term.
 // The stage and the theta scheme keep d and the coarse mass term of P v.
-template <int K, int FROM_PATCHES, bool OPAQUE_TID, bool CN = false>
+template <int K, int FROM_PATCHES, bool OPAQUE_TID, bool CN = false, int TF = kRhsFine>
 __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables tab)
 {
     static_assert(FROM_PATCHES != 2 || (K == 2 && !CN && !OPAQUE_TID), "tile frame: the one-launch K = 2 step, one tile per block");
@@ -244,12 +246,12 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
     const int tid = OPAQUE_TID ? tile_thread() : (int)threadIdx.x;
     constexpr int n = 1 << K;
     constexpr int nf = (n + 1) * (n + 1);
-    constexpr int TP = kRhsFine / n;          // patches per tile and direction
+    constexpr int TP = TF / n;          // patches per tile and direction
     constexpr int HP = TP + 2;                // with a ring of neighbour patches
-    constexpr int NO = kRhsFine + 1;          // tile nodes per direction
+    constexpr int NO = TF + 1;          // tile nodes per direction
     constexpr int SV = TP + 2;                // corner velocities: the tile's patches and the next column and row
     constexpr float inv_n = 1.0f / n;
-    static_assert(kRhsFine == kFrameLine, "one tile shape for the frame");
+    static_assert(FROM_PATCHES != 2 || TF == kFrameLine, "one tile shape for the frame");
 
     // the staged per-patch outputs (step) and, once the node pass has read
     // them, the averaged correction (or u) at the tile's nodes share one buffer
@@ -312,7 +314,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
     float2 v_r[VIT];
     double2 g_r[GIT];
     double2 map_r[3];
-    if constexpr (CN) load_map64<K>(f, tid, pi0, pj0, map_r);
+    if constexpr (CN) load_map64<K, TF>(f, tid, pi0, pj0, map_r);
 #pragma unroll
     for (int i = 0; i < VIT; ++i) {
         const int t = min(tid + i * kThreads, NV - 1);
@@ -326,11 +328,11 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         const int pa = min(pl % TP, nx - 1 - pi0), pb = min(pl / TP, ny - 1 - pj0);
         g_r[i] = gt[2 * (pb * nx + pa) + (t & 1)];
     }
-    // tile frame (FROM_PATCHES = 2): the deep nodes' u (li, lj in 2 .. kRhsFine - 2),
+    // tile frame (FROM_PATCHES = 2): the deep nodes' u (li, lj in 2 .. TF - 2),
     // the inner nodes' averaged d (threads < INNER) and, on the threads from
     // kThreads - EDGES on, the outputs of every patch at one boundary-line node
     typedef TileFrame<K> FR;
-    constexpr int DN = kRhsFine - 3, ND = DN * DN;
+    constexpr int DN = TF - 3, ND = DN * DN;
     constexpr int DIT = FROM_PATCHES == 2 ? (ND + kThreads - 1) / kThreads : 1;
     static_assert(FROM_PATCHES != 2 || FR::INNER <= kThreads - FR::EDGES, "inner and edge nodes on separate threads");
     float2 du[DIT];
@@ -501,7 +503,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
                 float px, py;
                 pv_of(li, lj, px, py);
                 u = make_float2(px + d.x, py + d.y);
-                if (!ROWS && (li < kRhsFine || I == NX) && (lj < kRhsFine || J == NY)) {
+                if (!ROWS && (li < TF || I == NX) && (lj < TF || J == NY)) {
                     ut[lj * up + li] = u;
                     if (f.dbar_out) (reinterpret_cast<float2 *>(f.dbar_out) + nt0)[lj * (NX + 1) + li] = d;
                 }
@@ -550,7 +552,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
                 float px, py;
                 pv_of(li, lj, px, py);
                 const float2 u = make_float2(px + d.x, py + d.y);
-                if ((li < kRhsFine || I == NX) && (lj < kRhsFine || J == NY)) {
+                if ((li < TF || I == NX) && (lj < TF || J == NY)) {
                     ut[lj * up + li] = u;
                     if (dout) dout[lj * (NX + 1) + li] = d;
                 }
@@ -612,7 +614,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         // the rest: the last node column and row of the tile's patches (the
         // tile's own last column and row, or the mesh end inside the tile)
         const int le = min(TP, nx - pi0) * n, me = min(TP, ny - pj0) * n;
-        static_assert(2 * kRhsFine + 1 <= kThreads, "one last-row/column node per thread");
+        static_assert(2 * TF + 1 <= kThreads, "one last-row/column node per thread");
         if (tid < le + me + 1) {
             const int li = tid <= me ? le : tid - me - 1, lj = tid <= me ? tid : me;
             dlast = node(li, lj, ulast);
@@ -640,7 +642,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         // the mesh ends there): a row of u in 16-byte stores (rows of the
         // state start on 128-byte lines), a row of d node by node on
         // neighbouring lanes (its rows are NX + 1 nodes)
-        const int cols = I0 + kRhsFine < NX ? kRhsFine : NX - I0 + 1, rows = J0 + kRhsFine < NY ? kRhsFine : NY - J0 + 1;
+        const int cols = I0 + TF < NX ? TF : NX - I0 + 1, rows = J0 + TF < NY ? TF : NY - J0 + 1;
         const float2 *const iu = UB ? s_dbar : s_other, *const id = UB ? s_other : s_dbar;
         constexpr int PR = (NO + 1) / 2;
         for (int t = tid; t < rows * PR; t += kThreads) {
@@ -666,7 +668,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
     }
     __syncthreads();
     if constexpr (CN) {
-        transport_corners<K>(f, tid, pi0, pj0, s_v, s_dbar, s_T, map_r);
+        transport_corners<K, TF>(f, tid, pi0, pj0, s_v, s_dbar, s_T, map_r);
         __syncthreads();
     }
     const double th_old = CN ? 1.0 - (double)f.theta : 0.0;
@@ -700,7 +702,7 @@ __device__ __forceinline__ void rhs_tile(const FlowArgs &f, int blk, RhsTables t
         // each step their reads fall in different LDS banks (patch rows lie a
         // multiple of 64 banks apart).  (At K = 3 the rotation's run-time row
         // index cost more than the conflicts it removed.)
-        constexpr int RR = TP >= 8 ? 2 : 1;
+        constexpr int RR = K <= 2 ? 2 : 1;
         const int rot = (pl / TP) % RR;
         double S[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
 #pragma unroll
@@ -769,10 +771,17 @@ template <int K>
 constexpr int rhs_waves() { return K == 1 ? 4 : 6; }
 
 // The theta scheme (Crank-Nicolson), single flow.
-template <int K, int FROM_PATCHES>
+template <int K, int FROM_PATCHES, int TF>
 __global__ __launch_bounds__(kThreads, 3) void k_rhs_cn(FlowArgs single, RhsTables tab)
 {
-    rhs_tile<K, FROM_PATCHES, false, true>(single, xcd_tile(blockIdx.x, gridDim.x), tab);
+    rhs_tile<K, FROM_PATCHES, false, true, TF>(single, xcd_tile(blockIdx.x, gridDim.x), tab);
+}
+
+// The single-flow step or stage on few tiles, in tiles of 16 x 16.
+template <int K, int FROM_PATCHES>
+__global__ __launch_bounds__(kThreads, 2) void k_rhs_small(FlowArgs single, RhsTables tab)
+{
+    rhs_tile<K, FROM_PATCHES, false, false, kRhsFew>(single, xcd_tile(blockIdx.x, gridDim.x), tab);
 }
 
 template <int K, int FROM_PATCHES, bool BATCHED>
@@ -853,10 +862,24 @@ hipError_t launch_rhs(const FlowArgs &f, const BatchTable *bt, int nblocks, int 
         else hipLaunchKernelGGL((k_rhs<2, 2, false>), g, b, 0, s, f, bt, tab);
         return hipGetLastError();
     }
+    // Few tiles: 16 x 16 elements each, so that a tile's FP64 sums spread over
+    // four times the workgroups.  GPU step times (us, tiles of 32 against 16): K = 1
+    // 16 x 16 patches 18.2 / 16.7, with Crank-Nicolson 23.1 / 20.0, 301 x 83 (114 tiles) 23.1 / 21.7
+    // and 27.6 / 25.3, 512 x 200 (416) 36.8 / 35.8 and 44.0 / 47.5; K = 2 60 x 40 21.5 / 20.3,
+    // 128 x 64 (128) 23.0 / 22.1 and 26.0 / 25.3, 200 x 100 (325) 30.4 / 29.9 and 36.2 / 40.0; K = 3
+    // 20 x 20 (25) 22.1 / 21.4, 60 x 40 (150) 23.6 / 23.2 and 28.4 / 29.4.
+    const bool few = !bt && nblocks <= num_cus() / (K == 3 ? 8 : 2);
 #define DNNMG_RHS_CASE(KK)                                                                \
     case KK:                                                                              \
-        if (cn && from_patches) hipLaunchKernelGGL((k_rhs_cn<KK, 1>), g, b, 0, s, f, tab); \
-        else if (cn) hipLaunchKernelGGL((k_rhs_cn<KK, 0>), g, b, 0, s, f, tab);           \
+        if (few) {                                                                        \
+            const int tp = kRhsFew >> KK;                                                 \
+            const dim3 gf(((f.nx + tp - 1) / tp) * ((f.ny + tp - 1) / tp));               \
+            if (cn && from_patches) hipLaunchKernelGGL((k_rhs_cn<KK, 1, kRhsFew>), gf, b, 0, s, f, tab); \
+            else if (cn) hipLaunchKernelGGL((k_rhs_cn<KK, 0, kRhsFew>), gf, b, 0, s, f, tab); \
+            else if (from_patches) hipLaunchKernelGGL((k_rhs_small<KK, 1>), gf, b, 0, s, f, tab); \
+            else hipLaunchKernelGGL((k_rhs_small<KK, 0>), gf, b, 0, s, f, tab);           \
+        } else if (cn && from_patches) hipLaunchKernelGGL((k_rhs_cn<KK, 1, kRhsFine>), g, b, 0, s, f, tab); \
+        else if (cn) hipLaunchKernelGGL((k_rhs_cn<KK, 0, kRhsFine>), g, b, 0, s, f, tab); \
         else if (bt) hipLaunchKernelGGL((k_rhs<KK, 1, true>), g, b, 0, s, f, bt, tab);    \
         else if (from_patches) hipLaunchKernelGGL((k_rhs<KK, 1, false>), g, b, 0, s, f, bt, tab); \
         else hipLaunchKernelGGL((k_rhs<KK, 0, false>), g, b, 0, s, f, bt, tab);           \
