@@ -243,18 +243,16 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
     m.rel32.assign(m.rel.begin(), m.rel.end());
     // Dirichlet mask
     m.mask.assign((size_t)m.Fn, 0);
-    std::unordered_map<uint64_t, int> dir;
+    std::vector<unsigned char> dir((size_t)m.E, 0);      // per edge
     for (int k = 0; k < ndir; ++k) {
         const int a = dir_edges[2 * k], b = dir_edges[2 * k + 1];
-        if (a < 0 || a >= nc || b < 0 || b >= nc || !edges.count(edge_key(a, b)))
-            return "a Dirichlet edge is not an edge of the mesh";
-        dir[edge_key(a, b)] = 1;
+        const auto it = a < 0 || a >= nc || b < 0 || b >= nc ? edges.end() : edges.find(edge_key(a, b));
+        if (it == edges.end()) return "a Dirichlet edge is not an edge of the mesh";
+        dir[it->second.index] = 1;
     }
     for (int e = 0; e < ne; ++e) {
-        const int *v = elems + 4 * e;
-        const int ends[4][2] = {{v[0], v[1]}, {v[1], v[2]}, {v[3], v[2]}, {v[0], v[3]}};
         for (int k = 0; k < 4; ++k) {
-            if (!dir.count(edge_key(ends[k][0], ends[k][1]))) continue;
+            if (!dir[eidx[4 * e + k]]) continue;
             for (int t = 0; t <= n; ++t) {
                 const int a = (k == 0 || k == 2) ? t : (k == 1 ? n : 0);
                 const int b = (k == 1 || k == 3) ? t : (k == 2 ? n : 0);
@@ -281,9 +279,7 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
             int &f = first[eidx[x]];
             if (f < 0) f = x;
             else { join(x, f); join(f, x); }
-            const int *v = elems + 4 * (size_t)(x / 4);
-            const int ends[4][2] = {{v[0], v[1]}, {v[1], v[2]}, {v[3], v[2]}, {v[0], v[3]}};
-            if (dir.count(edge_key(ends[x % 4][0], ends[x % 4][1]))) m.ecode[x / 4] |= kEdgeDirichlet << (8 * (x % 4));
+            if (dir[eidx[x]]) m.ecode[x / 4] |= kEdgeDirichlet << (8 * (x % 4));
         }
     }
     // gather lists (counting sort keeps patch order)
