@@ -16,7 +16,6 @@
 #include <cmath>
 #include <cstdint>
 #include <string>
-#include <unordered_map>
 #include <vector>
 
 namespace dnnmg {
@@ -82,12 +81,6 @@ DNNMG_UM_HD inline int edge_of_node(int n, int a, int b, int &t)
 
 namespace umesh_detail {
 
-inline uint64_t edge_key(int a, int b)
-{
-    const uint32_t lo = (uint32_t)(a < b ? a : b), hi = (uint32_t)(a < b ? b : a);
-    return ((uint64_t)lo << 32) | hi;
-}
-
 // Point at parameter s of the edge from node a to node b: straight, or the
 // arc of circle `circ` (angle linear in s, the shorter way round).
 inline void edge_point(const double *xy, int a, int b, double s, int circ, const double *circles, double *out)
@@ -126,9 +119,17 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
     m.corners.assign(elems, elems + 4 * (size_t)ne);
     // edges in order of first appearance; each used by at most two elements,
     // in opposite directions (a consistently oriented mesh)
-    struct EdgeUse { int index, uses, from; };
-    std::unordered_map<uint64_t, EdgeUse> edges;
-    edges.reserve(4 * (size_t)ne);
+    // (an edge is listed at its lower node: hi its other node, next the list)
+    struct EdgeUse { int hi, next, uses, from; };
+    std::vector<EdgeUse> edges;
+    edges.reserve(2 * (size_t)ne + (size_t)nc);
+    std::vector<int> head((size_t)nc, -1);
+    auto find_edge = [&](int a, int b) {
+        const int lo = a < b ? a : b, hi = a < b ? b : a;
+        int i = head[lo];
+        while (i >= 0 && edges[i].hi != hi) i = edges[i].next;
+        return i;
+    };
     std::vector<int> eidx(4 * (size_t)ne);
     for (int e = 0; e < ne; ++e) {
         const int *v = elems + 4 * e;
@@ -140,25 +141,26 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
         const int ends[4][2] = {{v[0], v[1]}, {v[1], v[2]}, {v[3], v[2]}, {v[0], v[3]}};
         const bool ccw[4] = {true, true, false, false};   // local edge direction along the element's boundary
         for (int k = 0; k < 4; ++k) {
-            const uint64_t key = edge_key(ends[k][0], ends[k][1]);
-            const int from = ccw[k] ? ends[k][0] : ends[k][1];   // where the counter-clockwise walk enters it
-            auto it = edges.find(key);
-            if (it == edges.end()) {
-                edges.emplace(key, EdgeUse{(int)edges.size(), 1, from});
-                eidx[4 * e + k] = (int)edges.size() - 1;
+            const int a = ends[k][0], b = ends[k][1], lo = a < b ? a : b, hi = a < b ? b : a;
+            const int from = ccw[k] ? a : b;             // where the counter-clockwise walk enters it
+            int i = find_edge(a, b);
+            if (i < 0) {
+                i = (int)edges.size();
+                edges.push_back(EdgeUse{hi, head[lo], 1, from});
+                head[lo] = i;
             } else {
-                if (it->second.uses >= 2) return "an edge is shared by more than two elements";
-                if (it->second.from == from) return "neighbouring elements are not oriented alike";
-                it->second.uses++;
-                eidx[4 * e + k] = it->second.index;
+                if (edges[i].uses >= 2) return "an edge is shared by more than two elements";
+                if (edges[i].from == from) return "neighbouring elements are not oriented alike";
+                edges[i].uses++;
             }
+            eidx[4 * e + k] = i;
         }
     }
     m.E = (int)edges.size();
     m.Fn = nc + m.E * (n - 1) + ne * (n - 1) * (n - 1);
     if ((double)m.Fn * 2 > 2e9 || (double)ne * nf > 2e9) return "mesh too large";
     // curved edges: endpoints on their circle, the edge in the mesh
-    std::unordered_map<uint64_t, int> curve;
+    std::vector<int> curve((size_t)m.E, -1);             // per edge
     for (int k = 0; k < ncurved; ++k) {
         const int a = curved[3 * k], b = curved[3 * k + 1], c = curved[3 * k + 2];
         if (a < 0 || a >= nc || b < 0 || b >= nc || c < 0 || c >= ncirc) return "curved edge index out of range";
@@ -168,13 +170,10 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
             if (std::fabs(d - circles[3 * c + 2]) > 1e-9 * circles[3 * c + 2])
                 return "a curved edge's node is not on its circle";
         }
-        if (!edges.count(edge_key(a, b))) return "a curved edge is not an edge of the mesh";
-        curve[edge_key(a, b)] = c;
+        const int i = find_edge(a, b);
+        if (i < 0) return "a curved edge is not an edge of the mesh";
+        curve[i] = c;
     }
-    auto curve_of = [&](int a, int b) {
-        auto it = curve.find(edge_key(a, b));
-        return it == curve.end() ? -1 : it->second;
-    };
     // fine nodes and patch maps
     m.fxy.assign(2 * (size_t)m.Fn, 0.0);
     m.pmap.assign((size_t)ne * nf, -1);
@@ -184,7 +183,7 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
         const int *v = elems + 4 * e;
         const int ends[4][2] = {{v[0], v[1]}, {v[1], v[2]}, {v[3], v[2]}, {v[0], v[3]}};
         int circ[4];
-        for (int k = 0; k < 4; ++k) circ[k] = curve_of(ends[k][0], ends[k][1]);
+        for (int k = 0; k < 4; ++k) circ[k] = curve[eidx[4 * e + k]];
         for (int b = 0; b <= n; ++b)
             for (int a = 0; a <= n; ++a) {
                 int f, k = -1, along = 0;
@@ -246,9 +245,9 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
     std::vector<unsigned char> dir((size_t)m.E, 0);      // per edge
     for (int k = 0; k < ndir; ++k) {
         const int a = dir_edges[2 * k], b = dir_edges[2 * k + 1];
-        const auto it = a < 0 || a >= nc || b < 0 || b >= nc ? edges.end() : edges.find(edge_key(a, b));
-        if (it == edges.end()) return "a Dirichlet edge is not an edge of the mesh";
-        dir[it->second.index] = 1;
+        const int i = a < 0 || a >= nc || b < 0 || b >= nc ? -1 : find_edge(a, b);
+        if (i < 0) return "a Dirichlet edge is not an edge of the mesh";
+        dir[i] = 1;
     }
     for (int e = 0; e < ne; ++e) {
         for (int k = 0; k < 4; ++k) {
@@ -323,9 +322,8 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
         g[0] = exx * eyy - eyx * exy;
         g[1] = exx * fy - fx * exy;
         g[2] = fx * eyy - eyx * fy;
-        const int ends[4][2] = {{v[0], v[1]}, {v[1], v[2]}, {v[3], v[2]}, {v[0], v[3]}};
         bool curved = false;
-        for (int k = 0; k < 4; ++k) curved = curved || curve_of(ends[k][0], ends[k][1]) >= 0;
+        for (int k = 0; k < 4; ++k) curved = curved || curve[eidx[4 * e + k]] >= 0;
         if (curved) m.cidx[e] = ncp++;
     }
     m.W.assign((size_t)ncp * 4 * nf, 0.0);
