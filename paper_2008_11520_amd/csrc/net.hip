@@ -43,16 +43,6 @@ template <> struct Op<0> {
         return acc;
     }
     __device__ static inline T cvt(float x) { return x; }
-    // A fragment from FP32 global memory (4 contiguous values).
-    __device__ static inline Frag load_f32(const float *p) { return *reinterpret_cast<const f4 *>(p); }
-    // A fragment of the network input (stored FP32 in this form).
-    __device__ static inline Frag load_x(const void *X, size_t off)
-    {
-        return *reinterpret_cast<const f4 *>(reinterpret_cast<const float *>(X) + off);
-    }
-    // The same through global address-space pointers.
-    __device__ static inline Frag load_f32(gptr<float> p) { return *(gptr<f4>)p; }
-    __device__ static inline Frag load_x(gptr<T> X, size_t off) { return *(gptr<f4>)(X + off); }
 };
 
 // BF16 operands: one 16x16x32 MFMA per 32-wide k-chunk.
@@ -65,29 +55,6 @@ template <> struct Op<1> {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
     }
     __device__ static inline T cvt(float x) { return (__bf16)x; }
-    __device__ static inline Frag load_f32(const float *p)
-    {
-        f4 u = *reinterpret_cast<const f4 *>(p), w = *reinterpret_cast<const f4 *>(p + 4);
-        Frag r;
-        r[0] = (__bf16)u.x; r[1] = (__bf16)u.y; r[2] = (__bf16)u.z; r[3] = (__bf16)u.w;
-        r[4] = (__bf16)w.x; r[5] = (__bf16)w.y; r[6] = (__bf16)w.z; r[7] = (__bf16)w.w;
-        return r;
-    }
-    // A fragment of the network input (stored BF16 in this form).
-    __device__ static inline Frag load_x(const void *X, size_t off)
-    {
-        return *reinterpret_cast<const bf8 *>(reinterpret_cast<const __bf16 *>(X) + off);
-    }
-    // The same through global address-space pointers.
-    __device__ static inline Frag load_f32(gptr<float> p)
-    {
-        f4 u = *(gptr<f4>)p, w = *(gptr<f4>)(p + 4);
-        Frag r;
-        r[0] = (__bf16)u.x; r[1] = (__bf16)u.y; r[2] = (__bf16)u.z; r[3] = (__bf16)u.w;
-        r[4] = (__bf16)w.x; r[5] = (__bf16)w.y; r[6] = (__bf16)w.z; r[7] = (__bf16)w.w;
-        return r;
-    }
-    __device__ static inline Frag load_x(gptr<T> X, size_t off) { return *(gptr<bf8>)(X + off); }
 };
 
 
