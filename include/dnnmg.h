@@ -273,7 +273,8 @@ int dnnmg_destroy(dnnmg_ctx *ctx);
  * that holds it, of that element's corner values; the defect and the mass
  * matrix are assembled over the fine elements (2 x 2 Gauss points on each
  * fine element's own bilinear map); a node's correction is the mean of the
- * outputs of every patch that holds it; R = P^T.  Patch-local node order and the
+ * outputs of every patch that holds it (a coarse node that no element uses: d = 0,
+ * u_prev = v there); R = P^T.  Patch-local node order and the
  * network input are those of the structured form, the features taken from
  * each element's four corners (hx the mean of edges (v0,v1), (v3,v2); hy of
  * (v0,v3), (v1,v2); hx / hy; the straight quadrilateral's area). */

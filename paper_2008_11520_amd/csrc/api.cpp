@@ -279,7 +279,8 @@ struct UMeshDev {
     float *rel = nullptr;
     double *dgeo = nullptr, *W = nullptr, *M4 = nullptr;
     int *cidx = nullptr;
-    int *enb = nullptr, *vocc = nullptr;
+    int *enb = nullptr, *vocc = nullptr, *lone = nullptr;
+    int nlone = 0;
     unsigned *ecode = nullptr;
     float *feat = nullptr, *uprev = nullptr, *dloc = nullptr;
     unsigned char *mask = nullptr;
@@ -718,6 +719,8 @@ UArgs uargs(const dnnmg_ctx *c, const float *v, const float *p)
     u.enb = m.enb;
     u.ecode = m.ecode;
     u.vocc = m.vocc;
+    u.lone = m.lone;
+    u.nlone = m.nlone;
     u.X = c->X();
     u.dpatch = c->dpatch();
     u.part = c->part();
@@ -899,7 +902,7 @@ extern "C" int dnnmg_create_umesh(const dnnmg_config *cfg, const dnnmg_umesh *me
     const size_t o_mask = take(m.mask.size()), o_up = take(sizeof(float) * 2 * (size_t)m.Fn);
     const size_t o_dloc = take(sizeof(float) * 2 * (size_t)m.ne * m.nf);
     const size_t o_enb = take(sizeof(int) * m.enb.size()), o_ec = take(sizeof(unsigned) * m.ecode.size());
-    const size_t o_vocc = take(sizeof(int) * m.vocc.size());
+    const size_t o_vocc = take(sizeof(int) * m.vocc.size()), o_lone = take(sizeof(int) * m.lone.size());
     auto bail = [&](int code) {
         (void)hipFree(c->ws);
         (void)hipFree(d->dev);
@@ -921,7 +924,8 @@ extern "C" int dnnmg_create_umesh(const dnnmg_config *cfg, const dnnmg_umesh *me
     d->mask = d->dev + o_mask; d->uprev = (float *)(d->dev + o_up);
     d->dloc = (float *)(d->dev + o_dloc);
     d->enb = (int *)(d->dev + o_enb); d->ecode = (unsigned *)(d->dev + o_ec);
-    d->vocc = (int *)(d->dev + o_vocc);
+    d->vocc = (int *)(d->dev + o_vocc); d->lone = (int *)(d->dev + o_lone);
+    d->nlone = (int)m.lone.size();
     rc = build_weights(g, weights, st, &c->w);
     if (rc) { c->w = nullptr; return bail(rc); }
     hipError_t e = hipSuccess;
@@ -937,6 +941,7 @@ extern "C" int dnnmg_create_umesh(const dnnmg_config *cfg, const dnnmg_umesh *me
     up(d->enb, m.enb.data(), sizeof(int) * m.enb.size());
     up(d->ecode, m.ecode.data(), sizeof(unsigned) * m.ecode.size());
     up(d->vocc, m.vocc.data(), sizeof(int) * m.vocc.size());
+    up(d->lone, m.lone.data(), sizeof(int) * m.lone.size());
     up(d->rel, m.rel32.data(), sizeof(float) * m.rel32.size());
     up(d->feat, m.feat.data(), sizeof(float) * m.feat.size());
     up(d->W, m.W.data(), sizeof(double) * m.W.size());

@@ -163,6 +163,8 @@ struct UArgs {
     const int *enb;                  // P x 4: the patch across each local edge, or -1
     const unsigned *ecode;           // P: eight bits per edge and corner (umesh_build.h)
     const int *vocc;                 // P x 4 x 4: the first gather-list entries of each corner
+    const int *lone;                 // nlone: coarse nodes that no patch holds
+    int nlone;
     int *first_flag;                 // nonzero before the first step (then u_prev := P v)
     float *uprev;                    // Fn x 2
     float *dloc;                     // P x nf x 2: each patch's element contributions to its nodes

@@ -502,6 +502,12 @@ __global__ __launch_bounds__(kThreads) void k_urhs(UArgs u, const float *dbar)
             const int occ0 = r.vo.x == kLongList ? u.node_occ[u.node_ptr[r.c]] : r.vo.x;
             put(p, l, d, occ0 == (e0 + p) * nf + l, r.c);
         }
+        // coarse nodes that no patch holds: no output to average, the correction is zero
+        for (int t = blockIdx.x * kThreads + tid; t < u.nlone; t += gridDim.x * kThreads) {
+            const int c = u.lone[t];
+            reinterpret_cast<float2 *>(u.uprev)[c] = reinterpret_cast<const float2 *>(u.v)[c];
+            if (u.dbar_out) reinterpret_cast<float2 *>(u.dbar_out)[c] = make_float2(0.f, 0.f);
+        }
         if (nonfin && u.nonfinite) atomicOr(u.nonfinite, 1);
         if (blockIdx.x == 0 && tid == 0) *u.first_flag = 0;   // the step's defect has read it (stream order)
     } else {

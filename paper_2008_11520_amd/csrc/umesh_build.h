@@ -39,6 +39,7 @@ struct UMeshHost {
     std::vector<int> enb;               // ne x 4
     std::vector<unsigned> ecode;        // ne
     std::vector<int> vocc;              // ne x 4 x 4
+    std::vector<int> lone;              // coarse nodes that no element has
     std::vector<float> feat;            // ne x 4: hx, hy, hx / hy, area
     // A patch with straight edges is the bilinear image of the reference
     // square, its fine elements those of the uniform sub-squares: its mass
@@ -298,6 +299,8 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
         if (cnt > 4) m.vocc[4 * (size_t)x] = kLongList;
         if (m.mask[f]) m.ecode[x / 4] |= kCornerDirichlet << (8 * (x % 4));
     }
+    for (int c = 0; c < nc; ++c)
+        if (m.node_ptr[c] == m.node_ptr[c + 1]) m.lone.push_back(c);
     m.cnode_ptr.assign((size_t)nc + 1, 0);
     for (int i = 0; i < 4 * ne; ++i) m.cnode_ptr[elems[i] + 1]++;
     for (int c = 0; c < nc; ++c) m.cnode_ptr[c + 1] += m.cnode_ptr[c];
