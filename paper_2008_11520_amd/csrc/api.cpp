@@ -1519,10 +1519,12 @@ extern "C" int dnnmg_batch_create(int max_flows, dnnmg_batch **out)
     return DNNMG_OK;
 }
 
+// All that a captured graph holds of the weight set by value.
 static bool same_net(const NetArgs &a, const NetArgs &b)
 {
     return a.K == b.K && a.H == b.H && a.Hm == b.Hm && a.nin == b.nin && a.nout == b.nout && a.prec == b.prec &&
-           a.kc1 == b.kc1 && a.B1 == b.B1 && a.B2 == b.B2 && a.B3 == b.B3 && a.B4 == b.B4;
+           a.kc1 == b.kc1 && a.B1 == b.B1 && a.B2 == b.B2 && a.B3 == b.B3 && a.B4 == b.B4 && a.s1 == b.s1 &&
+           a.s2 == b.s2 && a.s3 == b.s3 && a.s4 == b.s4 && a.xform == b.xform && a.reset_after == b.reset_after;
 }
 
 static void batch_drop_graph(dnnmg_batch *b)
