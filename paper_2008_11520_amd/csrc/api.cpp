@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -329,17 +330,20 @@ struct dnnmg_batch {
     int totals[kKinds] = {0, 0, 0, 0};
     NetArgs net{};
     RhsTables tab{};
-    int cap = 0;                                // grid of every batched launch in a graph
-    // grid of the one-tile-per-block launches (the one-launch tiles and the
-    // rhs after them; at K = 3 the defect and the rhs) in the captured graph: at least their tiles, grown
-    // (and the graph captured again) when a membership has more
-    int tile_grid = 0;
-    // captured launch sequence.  Every per-flow argument and the tile counts
-    // are read from `dev` at run time, so a graph stays valid while K, the X
+    int cap = 0;                                // grid of the launches that stride over the table's tiles, in a graph
+    // captured launch sequences.  Every per-flow argument and the tile counts
+    // are read from `dev` at run time, so they stay valid while K, the X
     // type, the gather and the shared weight set are unchanged, whichever
-    // flows fill the table.
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    // flows fill the table.  graphs[i] has cap << i blocks in the launches that take one
+    // tile per block (the one-launch tiles and the rhs after them; at K = 3 the
+    // defect and the rhs) and is captured when a membership first needs it: so
+    // no membership launches more than twice its tiles, or cap if it has fewer
+    // (one flow of 10 x 7 patches at K = 3, H = 128 after 64 flows of 128 x 128: 32.4 us a
+    // step; from a grid of 131072 blocks, twice the tiles of those 64 flows, 75.9).
+    struct Graph {
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+    } graphs[32];
     int graph_K = -1, graph_xfmt = -1, graph_gather = -1, graph_frame = -1;
     NetArgs graph_net{};
     RhsTables graph_tab{};
@@ -1529,10 +1533,11 @@ static bool same_net(const NetArgs &a, const NetArgs &b)
 
 static void batch_drop_graph(dnnmg_batch *b)
 {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
+    for (dnnmg_batch::Graph &g : b->graphs) {
+        if (g.exec) (void)hipGraphExecDestroy(g.exec);
+        if (g.graph) (void)hipGraphDestroy(g.graph);
+        g = dnnmg_batch::Graph();
+    }
     b->graph_gather = -1;
 }
 
@@ -1606,17 +1611,19 @@ extern "C" int dnnmg_batch_prepare(dnnmg_batch *b, dnnmg_ctx *const *ctxs, int n
     return DNNMG_OK;
 }
 
-// Grids of the batched launches.  The kernels stride over the table's tiles,
-// so any grid is correct; a graph uses the fixed cap so that one capture
-// serves every membership, an eager launch trims the grid to the work.
-static int batch_enqueue(dnnmg_batch *b, bool graph, hipStream_t st)
+// Grids of the batched launches.  The one-launch tiles, the rhs of the tile
+// frame and at K = 3 the defect and the rhs take one tile per block: a graph
+// (tile_grid > 0) gives them tile_grid blocks, which must be at least the
+// table's tiles, an eager launch as many as there are tiles.  The other
+// kernels stride over the table's tiles, so any grid is correct; a graph uses
+// the fixed cap, an eager launch trims the grid to the work.
+static int batch_enqueue(dnnmg_batch *b, int tile_grid, hipStream_t st)
 {
     FlowArgs dummy{};
+    const bool graph = tile_grid > 0;
     int grid[kKinds];
     for (int k = 0; k < kKinds; ++k) grid[k] = graph ? b->cap : std::min(b->totals[k], b->cap);
-    // the one-launch tiles, the rhs of the tile frame and at K = 3 the defect and
-    // the rhs take one tile per block
-    auto tiles = [&](int k) { return graph ? b->tile_grid : b->totals[k]; };
+    auto tiles = [&](int k) { return graph ? tile_grid : b->totals[k]; };
     if (fused_step(b->net)) {
         HIP_OR_FAIL(launch_defect_net(dummy, b->dev, tiles(kKindDefect), b->net, st));
     } else {
@@ -1634,26 +1641,32 @@ extern "C" int dnnmg_batch_launch(dnnmg_batch *b, int use_graph, void *stream)
     if (!b) return fail(DNNMG_EINVAL, "batch is NULL");
     if (!b->prepared) return fail(DNNMG_ESTATE, "dnnmg_batch_prepare has not been called");
     hipStream_t st = (hipStream_t)stream;
-    if (!use_graph) return batch_enqueue(b, false, st);
+    if (!use_graph) return batch_enqueue(b, 0, st);
     if (!st) return fail(DNNMG_EINVAL, "graph launches need a non-default stream");
     // (only the one-launch batches and K = 3 have one-tile-per-block launches)
     const int tiles = fused_step(b->net) || b->K == 3 ? std::max(b->totals[kKindDefect], b->totals[kKindRhs]) : 0;
-    const bool same = b->exec && b->graph_K == b->K && b->graph_xfmt == b->xfmt &&
-                      b->graph_gather == b->gather && b->graph_frame == b->frame && tiles <= b->tile_grid &&
+    const bool same = b->graph_K == b->K && b->graph_xfmt == b->xfmt &&
+                      b->graph_gather == b->gather && b->graph_frame == b->frame &&
                       same_net(b->graph_net, b->net) &&
                       b->graph_tab.A == b->tab.A && b->graph_tab.M == b->tab.M;
-    if (!same) {
-        batch_drop_graph(b);
-        if (tiles > b->tile_grid) b->tile_grid = std::max(b->cap, 2 * tiles);
+    if (!same) batch_drop_graph(b);
+    int gi = 0;
+    while (((long long)b->cap << gi) < tiles) ++gi;
+    dnnmg_batch::Graph &bg = b->graphs[gi];
+    if (!bg.exec) {
         HIP_OR_FAIL(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        int rc = batch_enqueue(b, true, st);
+        int rc = batch_enqueue(b, (int)std::min((long long)b->cap << gi, (long long)INT_MAX), st);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(st, &g);
         if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
         if (e != hipSuccess) return fail(DNNMG_EDEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e));
-        b->graph = g;
-        e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
-        if (e != hipSuccess) { batch_drop_graph(b); return fail(DNNMG_EDEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e)); }
+        e = hipGraphInstantiate(&bg.exec, g, nullptr, nullptr, 0);
+        if (e != hipSuccess) {
+            (void)hipGraphDestroy(g);
+            bg.exec = nullptr;
+            return fail(DNNMG_EDEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
+        }
+        bg.graph = g;
         b->graph_K = b->K;
         b->graph_xfmt = b->xfmt;
         b->graph_gather = b->gather;
@@ -1662,7 +1675,7 @@ extern "C" int dnnmg_batch_launch(dnnmg_batch *b, int use_graph, void *stream)
         b->graph_tab = b->tab;
         b->captures++;
     }
-    HIP_OR_FAIL(hipGraphLaunch(b->exec, st));
+    HIP_OR_FAIL(hipGraphLaunch(bg.exec, st));
     return DNNMG_OK;
 }
 
