@@ -120,15 +120,24 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
     m.corners.assign(elems, elems + 4 * (size_t)ne);
     // edges in order of first appearance; each used by at most two elements,
     // in opposite directions (a consistently oriented mesh)
-    // (an edge is listed at its lower node: hi its other node, next the list)
-    struct EdgeUse { int hi, next, uses, from; };
+    // (an edge is listed at the end with fewer elements, at its lower node where
+    // both have as many, so that a node of many elements makes no long list: other
+    // its other node, next the list.  20 000 elements around the mesh's first
+    // node, K = 2: the mesh is built in 14 ms; with the lower node's list in 584)
+    struct EdgeUse { int other, next, uses, from; };
     std::vector<EdgeUse> edges;
     edges.reserve(2 * (size_t)ne + (size_t)nc);
-    std::vector<int> head((size_t)nc, -1);
-    auto find_edge = [&](int a, int b) {
+    std::vector<int> head((size_t)nc, -1), valence((size_t)nc, 0);
+    for (size_t i = 0; i < 4 * (size_t)ne; ++i)
+        if (elems[i] >= 0 && elems[i] < nc) valence[elems[i]]++;
+    auto list_end = [&](int a, int b) {
         const int lo = a < b ? a : b, hi = a < b ? b : a;
-        int i = head[lo];
-        while (i >= 0 && edges[i].hi != hi) i = edges[i].next;
+        return valence[hi] < valence[lo] ? hi : lo;
+    };
+    auto find_edge = [&](int a, int b) {
+        const int at = list_end(a, b), other = at == a ? b : a;
+        int i = head[at];
+        while (i >= 0 && edges[i].other != other) i = edges[i].next;
         return i;
     };
     std::vector<int> eidx(4 * (size_t)ne);
@@ -142,13 +151,14 @@ inline std::string build_umesh(int nc, int ne, const double *xy, const int *elem
         const int ends[4][2] = {{v[0], v[1]}, {v[1], v[2]}, {v[3], v[2]}, {v[0], v[3]}};
         const bool ccw[4] = {true, true, false, false};   // local edge direction along the element's boundary
         for (int k = 0; k < 4; ++k) {
-            const int a = ends[k][0], b = ends[k][1], lo = a < b ? a : b, hi = a < b ? b : a;
+            const int a = ends[k][0], b = ends[k][1];
             const int from = ccw[k] ? a : b;             // where the counter-clockwise walk enters it
             int i = find_edge(a, b);
             if (i < 0) {
+                const int at = list_end(a, b);
                 i = (int)edges.size();
-                edges.push_back(EdgeUse{hi, head[lo], 1, from});
-                head[lo] = i;
+                edges.push_back(EdgeUse{at == a ? b : a, head[at], 1, from});
+                head[at] = i;
             } else {
                 if (edges[i].uses >= 2) return "an edge is shared by more than two elements";
                 if (edges[i].from == from) return "neighbouring elements are not oriented alike";
