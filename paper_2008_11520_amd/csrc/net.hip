@@ -159,7 +159,7 @@ __device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const Ne
         for (unsigned c0 = tid; c0 < np; c0 += U * NT) {
             u4 x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = X[min(c0 + u * NT, in - 1)];
+            for (int u = 0; u < U; ++u) x[u] = X[tile_piece_last(c0 + u * NT, in)];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const unsigned c = c0 + u * NT, r = c * inv >> 24;
@@ -171,7 +171,7 @@ __device__ __forceinline__ void stream_tile(const FlowArgs &f, int blk, const Ne
 #pragma unroll
     for (int q = 0; q < RT; ++q) {
         const int r = 16 * (rt0 + q) + li;
-        hold[q] = *(gf4 *)(hG + min(r, nrows - 1) * H + ucol);
+        hold[q] = *(gf4 *)(hG + tile_row(r, nrows) * H + ucol);
     }
     Frag w[AHEAD][3];
     const int kcx = (nin + KC - 1) / KC;            // chunks with input columns
@@ -1392,14 +1392,14 @@ __global__ __launch_bounds__(4 * H, 2) void k_net_wide(FlowArgs single, const Ba
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
             const int c = t0 + i * NT;
-            xr[i] = rw.X[min(c / XP, rw.nrows - 1) * XP + c % XP];
+            xr[i] = rw.X[tile_piece(c, XP, rw.nrows)];
         }
     };
     auto load_hold = [&](const Rows &rw) {
         const int l = tile_thread() & 63;
 #pragma unroll
         for (int q = 0; q < RTW; ++q)
-            hold[q] = *(const __attribute__((address_space(1))) f4 *)(rw.h + min(16 * q + (l & 15), rw.nrows - 1) * H +
+            hold[q] = *(const __attribute__((address_space(1))) f4 *)(rw.h + tile_row(16 * q + (l & 15), rw.nrows) * H +
                                                                        16 * ht + 4 * (l >> 4));
     };
     Rows rw{};

@@ -67,4 +67,20 @@ DNNMG_HD inline bool tile_piece_in(int c, int per_row, int nrows)
     return c < 64 * per_row && c / per_row < nrows;
 }
 
+// Unconditional reads (k_net, k_net_wide): row r of a tile with nrows rows,
+// rows past its end taken from its last row.  nrows <= 0: the second half of a
+// short 64-patch row tile, which starts 1 - nrows rows behind the flow's last row
+// and reads that row.
+DNNMG_HD inline int tile_row(int r, int nrows) { return min(r, nrows - 1); }
+
+// k_net_wide: piece c of per_row pieces per row.
+DNNMG_HD inline int tile_piece(int c, int per_row, int nrows)
+{
+    return tile_row(c / per_row, nrows) * per_row + c % per_row;
+}
+
+// k_net: piece c of the tile's `pieces` pieces of memory (at least one), pieces
+// past its end taken from the last one.
+DNNMG_HD inline unsigned tile_piece_last(unsigned c, unsigned pieces) { return min(c, pieces - 1u); }
+
 }  // namespace dnnmg
