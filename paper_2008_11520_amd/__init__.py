@@ -138,8 +138,9 @@ def workspace_bytes(cfg: Config) -> int:
 def _stream(stream):
     """The stream's handle; None: torch's current stream.  Small steps are as
     fast as the host enqueues them: torch.cuda.current_stream() builds a Stream
-    object on each call (3.0 us, twice a step; the handle alone 0.4 us; 32 x 8
-    patches, K = 2, 18.8 -> 17.3 us a step)."""
+    object on each call (2.9 us, twice a step; the handle alone 0.5 us).  Enqueueing
+    a step of 32 x 8 patches, K = 2: 17.9 -> 12.6 us (then the GPU's 17.9 bound it), of
+    16 x 16 patches, K = 1: 20.8 -> 15.2 us (the step 21.1 -> 19.3)."""
     import torch
     if stream is None:
         return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))

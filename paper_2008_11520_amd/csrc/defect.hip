@@ -543,7 +543,7 @@ __device__ __forceinline__ void fused_average(const FlowArgs &f, int tx, int ty,
     // the mesh end inside a ragged tile: its last node column li = le and row
     // lj = me (on a full tile these are boundary lines)
     const int le = min(TP, nx - pi0) * n, me = min(TP, ny - pj0) * n;
-    const int tl = NTH == kThreads ? tid : tid - kThreads;      // (threads that hold no node row, where there are some)
+    const int tl = NTH == kThreads ? tid : tid - kThreads;      // (small grids: the second 256 threads)
     if (tl >= 0 && tl < le + me + 1) {
         const int li = tl <= me ? le : tl - me - 1, lj = tl <= me ? tl : me;
         if (frame_kind(li, lj) != kFrameEdge) {
@@ -1148,17 +1148,16 @@ __global__ __launch_bounds__(kThreads, (defect_waves<K, XT>())) void k_defect(Fl
 }
 
 // The theta scheme (Crank-Nicolson) and/or the paper's network input, single flow.
-// (at K = 1 the paper's wider input rows leave LDS for one workgroup fewer)
-// (the theta scheme needs 114 to 117 registers; with 96 and 31 spilled 73 us
-// for 63 at 1024 x 256 and K = 2)
-template <int K, typename XT, bool CN, bool PAPER>
+// (the theta scheme needs 114 to 117 registers: at K = 3 four waves per SIMD, since
+// five spill; 512 x 256, H = 64, BF16: step 317 us, with five 376)
+template <int K, typename XT, bool CN>
 constexpr int defect_form_waves()
 {
-    return PAPER && K == 1 ? defect_waves<K, XT>() - 1 : (CN && K == 3 ? 4 : defect_waves<K, XT>());
+    return CN && K == 3 ? 4 : defect_waves<K, XT>();
 }
 
 template <int K, typename XT, bool CN, bool PAPER>
-__global__ __launch_bounds__(kThreads, (defect_form_waves<K, XT, CN, PAPER>())) void k_defect_form(FlowArgs single)
+__global__ __launch_bounds__(kThreads, (defect_form_waves<K, XT, CN>())) void k_defect_form(FlowArgs single)
 {
     defect_tile<K, XT, false, false, 0, CN, PAPER>(single, xcd_tile(blockIdx.x, gridDim.x));
 }
@@ -1188,6 +1187,10 @@ __global__ __launch_bounds__(kThreads, 4) void k_defect_net(FlowArgs single, con
 // 301 x 83, K = 1, Crank-Nicolson, paper input 19.0 -> 14.6 us.  The fused kernel, whose
 // weights take 96 KB of LDS, runs one tile per CU and only where there are no
 // more (375 tiles: step 26.2 us with 256-thread tiles, 30.3 us).
+// The rule is for a flow stepped by itself.  Eight flows of 256 tiles replayed at once
+// on eight streams leave no room for a tile more on a CU: 93 us a step of all of
+// them with 256-thread tiles, 107 us (two or four such flows: within 3 %); many
+// flows are stepped faster as a batch, which takes the 256-thread tiles.
 constexpr int kSmallThreads = 512;
 static bool defect_small(int ntiles, int per_cu)
 {

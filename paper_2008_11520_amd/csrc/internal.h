@@ -6,10 +6,10 @@
 
 namespace dnnmg {
 
-constexpr int kThreads = 256;     // every kernel: 4 wave64s per workgroup
+constexpr int kThreads = 256;     // 4 wave64s per workgroup: every kernel but the network's (by H) and the small-grid defects (512)
 constexpr int kTileFine = 32;     // defect tile: 32 x 32 fine elements
 constexpr int kRhsFine = 32;      // averaging / rhs tile: 32 x 32 fine elements
-constexpr int kNetRows = 64;      // GRU/MLP: patches per workgroup
+constexpr int kNetRows = 64;      // GRU/MLP: patches of a row tile (the unit that launches and the batch table count)
 constexpr int kMaxBatch = 256;    // flows per batched launch
 
 // Per-flow arguments of one step.  Passed by value for a single flow, or read

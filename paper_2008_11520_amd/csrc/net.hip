@@ -4,9 +4,9 @@
 //   h' = z h + (1 - z) tanh(W_h x + U_h (r h))
 //   d  = M2 relu(M1 h')   (or M h')
 //
-// Patches are the rows of tall-skinny products.  A workgroup takes 64 patch
-// rows (128 in the wide kernel); its waves own hidden tiles of 16 units and run
-// the whole chain on 16 x 16 MFMA tiles with FP32 accumulation:
+// Patches are the rows of tall-skinny products.  A workgroup takes tiles of 16, 32
+// or 64 patch rows (the batch table counts row tiles of 64); its waves own hidden
+// tiles of 16 units and run the whole chain on 16 x 16 MFMA tiles with FP32 accumulation:
 //   phase 1: [x | h] against the stacked gate weights [W_g | U_g] (U_h part 0),
 //   gates in registers, r*h to LDS,
 //   phase 2: (r*h) against U_h, then the update of h (FP32 state),
@@ -1539,14 +1539,16 @@ __global__ __launch_bounds__(4 * H, 2) void k_net_wide(FlowArgs single, const Ba
     }
 }
 
-// The persistent kernels take rows of the standard width 4 nf + 4 and the
-// GRU as printed; other forms run the generic kernels.
+// k_net_wide and k_net_q8p take rows of the standard width 4 nf + 4 and the GRU as
+// printed.
 static bool standard_rows(const NetArgs &net)
 {
     const int n = 1 << net.K;
     return net.nin == 4 * (n + 1) * (n + 1) + 4 && !net.reset_after;
 }
-// (H = 96 at K = 3 and other MLP widths run the streamed kernel)
+// k_net_reg takes the paper's rows and the reset after U_h as well; H = 32 and 96 at
+// K = 3, what k_net_wide leaves out at H = 128 or K = 3, and other MLP widths run the
+// streamed kernel.
 static bool use_reg(const NetArgs &net)
 {
     return net.prec == 1 && net.K <= 2 && net.H <= 96 && (net.Hm == 0 || net.Hm == net.H) &&

@@ -17,7 +17,9 @@ namespace dnnmg {
 using std::min;
 #endif
 
-// One 16-byte piece of the copy of a 128-patch tile's input rows into LDS.
+// One 16-byte piece of the copy of a 128-patch tile's input rows into LDS (no
+// kernel has tiles of 128 patches now; wide_x_piece and wide_h_row are replayed by
+// the host check alone).
 // The tile is two halves of up to 64 rows each (a: na >= 1
 // rows, b: nb >= 0 rows); a row is XP pieces of 8 BF16 (nin = 8 XP).  Wave
 // load i of wave w moves the pieces 64 j .. 64 j + 63 of the tile's 2 XP
@@ -59,8 +61,9 @@ DNNMG_HD inline int wide_h_row(int r, int na, int nb, int &half)
     return min(r & 63, (half ? nb : na) - 1);
 }
 
-// Predicate of the register prefetch of a 64-patch tile (k_net_reg,
-// k_net_q8p): piece c of per_row pieces per row is read when it lies in the
+// Predicate of the register prefetch of a tile of 64 patches (k_net_reg) or 32
+// (k_net_q8p, nrows <= 32; none or negative for the second half of a short row
+// tile): piece c of per_row pieces per row is read when it lies in the
 // tile (c < 64 per_row) and in one of its nrows rows; other pieces are zero.
 DNNMG_HD inline bool tile_piece_in(int c, int per_row, int nrows)
 {

@@ -4,9 +4,9 @@
 // Per step (the fine part of Alg. 2), all data addressed through the patch maps:
 //   k_udefect  one thread per fine element: the element residual of the
 //              defect (quad_residual: its own bilinear map and nodal P v, P p,
-//              u_prev, formed once per patch node in LDS), summed per
-//              patch-local node in four colour rounds (elements of one colour
-//              share no node);
+//              u_prev, formed once per patch node in LDS); every patch-local
+//              node then adds its up to four elements' shares in the order
+//              of their parity;
 //   k_unode    one thread per fine node: the patches' contributions summed in
 //              patch order (node_occ), zero at Dirichlet nodes (the stage
 //              entry point);
@@ -27,9 +27,9 @@
 // deterministic.  A node inside a patch edge has at most two patches: the other
 // one's entry is found through the patch's neighbour table (enb, ecode), one
 // dependent load where the node's gather list takes three; a sum of two terms
-// from +0 does not depend on their order.  Corners take their gather lists.  P v at a fine node is the bilinear interpolation, in the
-// reference coordinates of the first patch that holds the node, of that
-// patch's corner values.
+// from +0 does not depend on their order.  Corners take their gather lists.
+// P v at a fine node is the bilinear interpolation, in the reference coordinates
+// of the first patch that holds the node, of that patch's corner values.
 #include "device.h"
 #include "element.h"
 #include "internal.h"
